@@ -32,9 +32,10 @@ struct tvq_codec {
   tvq::SegParams* d_segs = nullptr;
   uint32_t* d_sign_masks = nullptr;
   float* d_lut = nullptr;
-  uint32_t* d_abins = nullptr;               // angle bins of n = 64, then n = 256 (pairs)
+  uint32_t* d_abins = nullptr;               // angle bins of n = 64, 256, 128 (pairs)
   uint32_t* d_seg_lists = nullptr;           // fast-format segment ids, then the others
-  uint32_t n_fast = 0, n_generic = 0;
+  uint32_t n_mfma = 0, n_fast = 0, n_generic = 0;   // segment list: the first n_mfma of the
+                                                    // n_fast also suit tvq_encode_mfma
 };
 
 // Scratch of tvq_attention_decode_noalloc: the attention partials of one call, in a static
@@ -476,7 +477,12 @@ tvq_status tvq_create(const tvq_config* cfg, tvq_codec** out) {
   // segment lists of the two decode kernels
   std::vector<uint32_t> lists;
   for (uint32_t i = 0; i < c->segs.size(); ++i)
-    if (tvq::fast_format(c->segs[i].n, c->segs[i].mode, c->segs[i].bits)) lists.push_back(i);
+    if (tvq::attn_format(c->segs[i].n, c->segs[i].mode, c->segs[i].bits)) lists.push_back(i);
+  c->n_mfma = (uint32_t)lists.size();
+  for (uint32_t i = 0; i < c->segs.size(); ++i)
+    if (tvq::fast_format(c->segs[i].n, c->segs[i].mode, c->segs[i].bits) &&
+        !tvq::attn_format(c->segs[i].n, c->segs[i].mode, c->segs[i].bits))
+      lists.push_back(i);
   c->n_fast = (uint32_t)lists.size();
   for (uint32_t i = 0; i < c->segs.size(); ++i)
     if (!tvq::fast_format(c->segs[i].n, c->segs[i].mode, c->segs[i].bits)) lists.push_back(i);
@@ -487,7 +493,7 @@ tvq_status tvq_create(const tvq_config* cfg, tvq_codec** out) {
   const size_t lut_bytes = lut.size() * sizeof(float);
   // angle bins of the fast formats' codebooks, as (code, boundary bits) pairs
   std::vector<uint32_t> abins;
-  for (int32_t n : {64, 256}) {
+  for (int32_t n : {64, 256, 128}) {
     std::vector<uint32_t> code(2 * n);
     std::vector<float> bound(2 * n);
     tvq_make_angle_bins(n, code.data(), bound.data());
@@ -575,7 +581,7 @@ static tvq_status encode_launch(const tvq_codec* c, tvq::EncodeArgs& a, const tv
   const uint32_t vpw = tvq::kWave / (c->d / tvq::kElemsPerLane);
   // bf16 input of the common formats goes to the multi-tile kernel, the rest to the generic
   // one (the segment list holds the common formats first, so all of it is every segment)
-  const uint32_t n_fast = f32 ? 0u : c->n_fast;
+  const uint32_t n_fast = f32 ? 0u : a.mfma_front ? c->n_mfma : c->n_fast;
   const struct { uint32_t first, count, tpw; bool fast; } launches[2] = {
       {0, n_fast, tvq::kFastTilesPerWave, true},
       {n_fast, c->n_fast + c->n_generic - n_fast, 1, false}};
@@ -583,6 +589,7 @@ static tvq_status encode_launch(const tvq_codec* c, tvq::EncodeArgs& a, const tv
     if (l.count == 0) continue;
     a.seg_list = c->d_seg_lists + l.first;
     a.num_segs = l.count;
+    a.has_n128 = l.fast && l.count > c->n_mfma ? 1u : 0u;
     const unsigned grid = plan_grid(a.nvec, vpw, a.num_segs, &a.waves_per_seg, &a.tiles_per_wave,
                                     l.tpw);
     const int rc = tvq_launch_encode(a, c->d, f32, l.fast, grid, stream);
@@ -843,7 +850,7 @@ static tvq_status attn_formats(const tvq_codec* c, int32_t layer, int (&fmt)[2])
   if (layer < 0 || layer >= c->L) return TVQ_ERR_INVALID_ARG;
   for (int kind = 0; kind < 2; ++kind) {
     const tvq::SegParams& sp = c->segs[2 * layer + kind];
-    if (!tvq::fast_format(sp.n, sp.mode, sp.bits)) return TVQ_ERR_UNSUPPORTED;
+    if (!tvq::attn_format(sp.n, sp.mode, sp.bits)) return TVQ_ERR_UNSUPPORTED;
     fmt[kind] = (sp.n == 256 ? 1 : 0) | (sp.mode == 2 ? 2 : 0);
   }
   return TVQ_OK;

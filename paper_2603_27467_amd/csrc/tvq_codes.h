@@ -152,8 +152,8 @@ __device__ __forceinline__ void log_level_ladder_each(Store&& store, int sub, fl
   ladder_levels_each<LPV, COUNT>(store, sub, rmin, rmax, ladder_rho(rmin, rmax, qlevels), qlevels);
 }
 
-// Raw code words of one vector's lane for n = 64/256 angle codes (WA = 6/8 bits) and NB = 8
-// linear or NB = 4 log-space norm codes: WA/2 + NB/2 + 2 registers.
+// Raw code words of one vector's lane for n = 64/128/256 angle codes (WA = 6/7/8 bits) and
+// NB = 8 linear or NB = 4 log-space norm codes: (WA + 1)/2 + NB/2 + 2 registers.
 template <int WA, int NB>
 struct TileCodes {
   Chunk<WA> ang;
@@ -166,7 +166,7 @@ __device__ __forceinline__ TileCodes<WA, NB> load_codes_at(const uint8_t* const 
                                                            const uint32_t (&rec)[3], uint32_t slot,
                                                            int sub) {
   TileCodes<WA, NB> c;
-  c.ang = load_chunk<WA>(plane[0] + (uint64_t)slot * rec[0] + 2 * WA * sub);
+  c.ang = load_lane_chunk<WA>(plane[0] + (uint64_t)slot * rec[0], 0u, sub);
   c.nrm = load_chunk<NB>(plane[1] + (uint64_t)slot * rec[1] + 2 * NB * sub);
   c.hdr = *(const u32x2*)(plane[2] + (uint64_t)slot * 8);
   return c;
@@ -180,7 +180,7 @@ __device__ __forceinline__ TileCodes<WA, NB> load_codes_from(const uint8_t* cons
                                                              const uint32_t (&rec)[3],
                                                              uint32_t slot0, uint32_t j, int sub) {
   TileCodes<WA, NB> c;
-  c.ang = load_chunk<WA>(plane[0] + (uint64_t)slot0 * rec[0] + (j * rec[0] + 2 * WA * sub));
+  c.ang = load_lane_chunk<WA>(plane[0] + (uint64_t)slot0 * rec[0], j * rec[0], sub);
   c.nrm = load_chunk<NB>(plane[1] + (uint64_t)slot0 * rec[1] + (j * rec[1] + 2 * NB * sub));
   c.hdr = *(const u32x2*)(plane[2] + (uint64_t)slot0 * 8 + j * 8);
   return c;

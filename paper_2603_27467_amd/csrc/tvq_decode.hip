@@ -21,7 +21,7 @@
 // A lane computes 32 consecutive elements of a vector (d/32 lanes per vector, 64/(d/32)
 // vectors per wave, a "tile").  Two kernels, each launched over its own list of (layer, kind)
 // segments so that each gets the register allocation its own work needs:
-//   decode_fast_kernel     n = 64 or 256 with 8-bit linear or 4-bit log norms.  A wave decodes
+//   decode_fast_kernel     n = 64, 128 or 256 with 8-bit linear or 4-bit log norms.  A wave decodes
 //                          several consecutive tiles and loads the next tile's code words while
 //                          decoding the current one: load latency otherwise dominates.  The
 //                          ladder ratio comes from a division-free Newton iteration, which keeps
@@ -446,13 +446,14 @@ __global__ __launch_bounds__(kBlockThreads) void decode_fast_kernel(DecodeArgs a
   }
   // every codebook of this kernel (n <= 256) is in LDS
   uint32_t* stg = s_stg[w.wib];
-  const bool wide = w.sp.w == 8;
   if (w.sp.mode == 1) {
-    if (wide) decode_tiles_prefetch<D, F32OUT, MULTI, 8, 8, ROWS, PAGED>(a, w, stg, tile0, ntiles);
-    else decode_tiles_prefetch<D, F32OUT, MULTI, 6, 8, ROWS, PAGED>(a, w, stg, tile0, ntiles);
+    if (w.sp.w == 6) decode_tiles_prefetch<D, F32OUT, MULTI, 6, 8, ROWS, PAGED>(a, w, stg, tile0, ntiles);
+    else if (w.sp.w == 7) decode_tiles_prefetch<D, F32OUT, MULTI, 7, 8, ROWS, PAGED>(a, w, stg, tile0, ntiles);
+    else decode_tiles_prefetch<D, F32OUT, MULTI, 8, 8, ROWS, PAGED>(a, w, stg, tile0, ntiles);
   } else {
-    if (wide) decode_tiles_prefetch<D, F32OUT, MULTI, 8, 4, ROWS, PAGED>(a, w, stg, tile0, ntiles);
-    else decode_tiles_prefetch<D, F32OUT, MULTI, 6, 4, ROWS, PAGED>(a, w, stg, tile0, ntiles);
+    if (w.sp.w == 6) decode_tiles_prefetch<D, F32OUT, MULTI, 6, 4, ROWS, PAGED>(a, w, stg, tile0, ntiles);
+    else if (w.sp.w == 7) decode_tiles_prefetch<D, F32OUT, MULTI, 7, 4, ROWS, PAGED>(a, w, stg, tile0, ntiles);
+    else decode_tiles_prefetch<D, F32OUT, MULTI, 8, 4, ROWS, PAGED>(a, w, stg, tile0, ntiles);
   }
 }
 

@@ -331,6 +331,30 @@ __device__ __forceinline__ void store_chunk(uint8_t* p, const Chunk<W>& o) {
   }
 }
 
+// Chunk of lane `sub` (2W bytes at 2W*sub of the record at `rec`), for the kernels of fixed
+// formats.  W = 7: the 14 bytes of an odd lane start 2 bytes past a dword, so a lane moves the 16
+// bytes that start on a dword and end (odd lanes) or begin (even lanes) with its own; what it
+// reads past its chunk belongs to its neighbour in the same record, and the dword that the
+// chunks of lanes 2i and 2i + 1 share is stored by both with the same value (the neighbour's
+// half by DPP).  One 16-byte access instead of seven 2-byte ones.
+template <int W>
+__device__ __forceinline__ void store_lane_chunk(uint8_t* rec, uint32_t lane_off, int sub,
+                                                 const Chunk<W>& o) {
+  if constexpr (W != 7) {
+    store_chunk<W>(rec + (lane_off + 2u * W * (uint32_t)sub), o);
+  } else {
+    const bool odd = (sub & 1) != 0;
+    const uint32_t p0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)o.w[0], 0xB1, 0xF, 0xF, true);
+    const uint32_t p3 = (uint32_t)__builtin_amdgcn_mov_dpp((int)o.w[3], 0xB1, 0xF, 0xF, true);
+    const uint32_t mid = odd ? p3 | (o.w[0] << 16) : o.w[3] | (p0 << 16);   // w[3] < 2^16
+    const uint32_t w[4] = {odd ? mid : o.w[0],
+                           odd ? __builtin_amdgcn_alignbit(o.w[1], o.w[0], 16) : o.w[1],
+                           odd ? __builtin_amdgcn_alignbit(o.w[2], o.w[1], 16) : o.w[2],
+                           odd ? __builtin_amdgcn_alignbit(o.w[3], o.w[2], 16) : mid};
+    store_words<4>((uint32_t*)(rec + (lane_off + 14u * (uint32_t)sub - (odd ? 2u : 0u))), w);
+  }
+}
+
 template <int W>
 __device__ __forceinline__ Chunk<W> load_chunk(const uint8_t* p) {
   Chunk<W> o;
@@ -344,6 +368,23 @@ __device__ __forceinline__ Chunk<W> load_chunk(const uint8_t* p) {
     for (int i = 0; i < W; ++i) o.w[i >> 1] |= (uint32_t)q[i] << (16 * (i & 1));
   }
   return o;
+}
+
+template <int W>
+__device__ __forceinline__ Chunk<W> load_lane_chunk(const uint8_t* rec, uint32_t lane_off,
+                                                    int sub) {
+  if constexpr (W != 7) {
+    return load_chunk<W>(rec + (lane_off + 2u * W * (uint32_t)sub));
+  } else {
+    const uint32_t odd = (uint32_t)sub & 1u;
+    uint32_t w[4];
+    load_words<4>((const uint32_t*)(rec + (lane_off + 14u * (uint32_t)sub - 2u * odd)), w);
+    Chunk<W> o;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) o.w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], 16u * odd);
+    o.w[3] = w[3] >> (16u * odd);
+    return o;
+  }
 }
 
 }  // namespace tvq

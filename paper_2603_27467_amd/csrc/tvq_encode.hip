@@ -8,7 +8,7 @@
 // vectors per wave, a "tile").  LDS holds per-wave tables only (the layer's sign masks, the
 // angle bins of the fast formats); no barriers: every wave is independent.  Two kernels, each
 // launched over its own list of (layer, kind) segments:
-//   encode_fast_kernel     bf16 input, n = 64 or 256 with 8-bit linear or 4-bit log norms,
+//   encode_fast_kernel     bf16 input, n = 64, 128 or 256 with 8-bit linear or 4-bit log norms,
 //                          every format constant known at compile time.  A wave encodes
 //                          several consecutive tiles, loading the next tile's input while it
 //                          encodes the current one, and amortizes its set-up over them.
@@ -321,7 +321,7 @@ __device__ __forceinline__ bool enc_wave_setup(const EncodeArgs& a, EncWave<D>& 
   w.bins_row = nullptr;
   w.bins_addr = 0;
   w.bins_off = 0;
-  if (bins_rows != nullptr && (w.sp.n == 64 || w.sp.n == 256)) {
+  if (bins_rows != nullptr && (w.sp.n == 64 || w.sp.n == 128 || w.sp.n == 256)) {
     w.bins_row = bins_rows[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];   // uniform
     w.bins_addr = (uint32_t)(uintptr_t)(lds_bins_ptr)w.bins_row - 8u * kRoundShiftBits;
   }
@@ -341,7 +341,7 @@ __device__ __forceinline__ void stage_tables(const EncodeArgs& a, const EncWave<
   const int lane = threadIdx.x & (kWave - 1);
   if (lane < D / 2) w.sm_row[lane] = a.sign_masks[(size_t)w.sp.layer * (D / 2) + lane];
   if (w.bins_row != nullptr) {
-    const u32x2* src = (const u32x2*)a.abins + (w.sp.n == 64 ? 0 : 2 * 64);
+    const u32x2* src = (const u32x2*)a.abins + (w.sp.n == 64 ? 0 : w.sp.n == 256 ? 2 * 64 : 2 * (64 + 256));
     for (uint32_t e = (uint32_t)lane; e < 2 * w.sp.n; e += kWave) w.bins_row[e] = src[e];
   }
   wave_lds_sync();
@@ -695,7 +695,7 @@ __device__ __forceinline__ bool encode_tile(const EncodeArgs& a, const EncWave<D
   const bool store = !PAGED || in.ok;
   constexpr int LPV = EncWave<D>::LPV;
   constexpr bool kFixed = WA != 0;
-  static_assert(!kFixed || ((WA == 6 || WA == 8) && (NB == 8 || NB == 4)), "fixed formats");
+  static_assert(!kFixed || ((WA == 6 || WA == 7 || WA == 8) && (NB == 8 || NB == 4)), "fixed formats");
   const SegParams& sp = w.sp;
   const float nf = kFixed ? (float)(1u << WA) : sp.nf;
   const uint32_t n = kFixed ? (1u << WA) : sp.n;
@@ -820,7 +820,7 @@ __device__ __forceinline__ bool encode_tile(const EncodeArgs& a, const EncWave<D
   if (store) {
     if constexpr (kFixed) {
       const uint32_t lane_ang = ALIGNED ? (uint32_t)w.vslot * sp.rec[0] : 0u;
-      store_chunk<WA>(rec_ang + (lane_ang + 2u * WA * (uint32_t)w.sub), pack16<WA>(kc));
+      store_lane_chunk<WA>(rec_ang, lane_ang, w.sub, pack16<WA>(kc));
     } else {
       store_codes_any(rec_ang, w.sub, sp.w, kc);
     }
@@ -883,8 +883,11 @@ __global__ __launch_bounds__(kBlockThreads) void encode_mfma_kernel(EncodeArgs a
   }
 }
 
-// ALIGNED: see load_tile (multi-tile launches only).
-template <int D, bool MULTI, bool PAGED, bool ALIGNED = false>
+// ALIGNED: see load_tile (multi-tile launches only).  N128: the segment list holds n = 128
+// segments; launches without them use the instantiation without that format's two tile loops,
+// whose presence costs the others 2% (the 32-layer n = 64 prefill of 4096 tokens at d = 128:
+// 156.0 us without, 159.5 us with).
+template <int D, bool MULTI, bool PAGED, bool ALIGNED = false, bool N128 = false>
 __global__ __launch_bounds__(kBlockThreads) void encode_fast_kernel(EncodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t s_sm[kWavesPerBlock][D / 2];
   __shared__ u32x2 s_bins[kWavesPerBlock][kBinRows];
@@ -893,6 +896,15 @@ __global__ __launch_bounds__(kBlockThreads) void encode_fast_kernel(EncodeArgs a
   if (!enc_wave_setup<D>(a, w, s_sm, tile0, ntiles, MULTI ? s_bins : nullptr)) return;
   static_assert(!(PAGED && ALIGNED) || MULTI, "aligned tiles: multi-tile launches");
   if constexpr (PAGED && ALIGNED) paged_records<D>(a, w, tile0, ntiles);
+  if constexpr (N128) {
+    if (w.sp.w == 7) {
+      if (w.sp.mode == 1)
+        encode_tiles_fast<D, MULTI, 7, 8, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
+      else
+        encode_tiles_fast<D, MULTI, 7, 4, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
+      return;
+    }
+  }
   const bool wide = w.sp.w == 8;
   if (w.sp.mode == 1) {
     if (wide) encode_tiles_fast<D, MULTI, 8, 8, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
@@ -918,6 +930,17 @@ __global__ __launch_bounds__(kBlockThreads) void encode_generic_kernel(EncodeArg
     encode_norms_f64<D, F32IN, 0, PAGED, false, false>(w, in);
 }
 
+template <int D, bool PAGED, bool N128>
+void launch_fast(const EncodeArgs& a, bool multi, bool aligned, unsigned grid, hipStream_t s) {
+  const dim3 g(grid), block(kBlockThreads);
+  if (multi && aligned)
+    hipLaunchKernelGGL((encode_fast_kernel<D, true, PAGED, true, N128>), g, block, 0, s, a);
+  else if (multi)
+    hipLaunchKernelGGL((encode_fast_kernel<D, true, PAGED, false, N128>), g, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((encode_fast_kernel<D, false, PAGED, false, N128>), g, block, 0, s, a);
+}
+
 template <int D, bool PAGED>
 void launch_encode(const EncodeArgs& a, int in_f32, bool fast, unsigned grid, hipStream_t s) {
   const dim3 block(kBlockThreads);
@@ -933,12 +956,10 @@ void launch_encode(const EncodeArgs& a, int in_f32, bool fast, unsigned grid, hi
   // tile's first vector, (VPW - 1) * stride_t + d elements of bf16, inside 32 bits
   constexpr uint32_t VPW = EncWave<D>::VPW;
   const bool aligned = a.div_t.div % VPW == 0 && (uint64_t)a.stride_t * VPW * 2u < (1ull << 31);
-  if (fast && multi && aligned)
-    hipLaunchKernelGGL((encode_fast_kernel<D, true, PAGED, true>), dim3(grid), block, 0, s, a);
-  else if (fast && multi)
-    hipLaunchKernelGGL((encode_fast_kernel<D, true, PAGED>), dim3(grid), block, 0, s, a);
+  if (fast && a.has_n128)
+    launch_fast<D, PAGED, true>(a, multi, aligned, grid, s);
   else if (fast)
-    hipLaunchKernelGGL((encode_fast_kernel<D, false, PAGED>), dim3(grid), block, 0, s, a);
+    launch_fast<D, PAGED, false>(a, multi, aligned, grid, s);
   else if (in_f32)
     hipLaunchKernelGGL((encode_generic_kernel<D, true, PAGED>), dim3(grid), block, 0, s, a);
   else

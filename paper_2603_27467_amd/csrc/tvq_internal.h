@@ -72,7 +72,7 @@ struct EncodeArgs {
   const SegParams* segs;
   const uint32_t* seg_list;  // segment indices this launch covers
   const uint32_t* sign_masks;
-  const uint32_t* abins;  // angle bins (code, boundary) of n = 64 (2 x 64), then n = 256
+  const uint32_t* abins;  // angle bins (code, boundary) of n = 64 (2 x 64), 256, 128
   FastDiv div_t, div_h;  // by T (tokens in the call) and by H
   uint32_t H;
   uint32_t nvec;         // B * H * T vectors per segment
@@ -81,6 +81,7 @@ struct EncodeArgs {
   uint32_t num_segs;
   float inv_d;           // 1/d (exact)
   Paging pg;             // paged destination (the paged entry point only)
+  uint32_t has_n128;     // the segment list names n = 128 segments
   uint32_t mfma_front;   // fast formats through the matrix-core front end (tvq_encode_mfma)
 };
 
@@ -136,11 +137,19 @@ constexpr uint32_t kAttnMaxGroup = 64;      // query heads per KV head
 // holds at once, so that every wave slot stays busy until the launch's end.
 constexpr int64_t kAttnRounds = 1;
 
-// Segments the multi-tile encode and decode kernels handle: n = 64 or 256 (6- or 8-bit angle
-// codes, every code a valid bin) with 8-bit linear or 4-bit log-space norms.  Other formats go
-// to the single-tile generic kernels.
-inline bool fast_format(uint32_t n, uint32_t mode, uint32_t bits) {
+// Formats of the attention kernels and of the matrix-core encode: n = 64 or 256 (6- or 8-bit
+// angle codes, every code a valid bin) with 8-bit linear or 4-bit log-space norms.
+inline bool attn_format(uint32_t n, uint32_t mode, uint32_t bits) {
   return (n == 64 || n == 256) && ((mode == 1 && bits == 8) || (mode == 2 && bits == 4));
+}
+
+// Segments the multi-tile encode and decode kernels handle: the same norms with n = 64, 128 or
+// 256.  Other formats go to the single-tile generic kernels.  n = 128 is here since its 14-byte
+// chunks move as one aligned 16-byte access per lane (load_lane_chunk): a 22-layer d = 64 cache
+// of 4 x 4097 tokens in the TinyLlama preset decodes in 108 us, 156 us with its n = 128 segments
+// on the generic kernel; the Mistral-7B preset prefill of 1999 tokens takes 84 us against 99.
+inline bool fast_format(uint32_t n, uint32_t mode, uint32_t bits) {
+  return attn_format(n == 128 ? 64 : n, mode, bits);
 }
 
 constexpr uint32_t kFastTilesPerWave = 4;

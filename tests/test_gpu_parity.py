@@ -523,6 +523,84 @@ def test_multi_tile_encode_sampled(gpu, d, L, B, T, t_begin, pad):
     assert stats["hdr_ulp"] <= 2
 
 
+@pytest.mark.parametrize("d,L,B,T,t_begin", [
+    (128, 2, 2, 4112, 5),        # whole tiles per (batch, head), two tiles per wave
+    (128, 2, 2, 4101, 3),        # ragged rows
+    (64, 2, 2, 8197, 0),
+    (64, 2, 1, 33, 2),           # one tile per wave, a tile of one vector
+])
+def test_n128_multi_tile(gpu, d, L, B, T, t_begin):
+    """n = 128 (7-bit codes: 14-byte chunks, odd lanes starting between dwords) with both norm
+    modes through the multi-tile kernels, contiguous and through a pool in shuffled blocks:
+    codes and headers of the last tiles of every segment and of 600 random vectors against the
+    oracle's encode, slots outside the range untouched, the same codes from the pool, and the
+    decoded values of those vectors (fp32 and bf16) against the oracle's decode of the bytes."""
+    import torch
+    H = 4 if T > 100 else 2
+    table = [LayerCfg(128, 128), LayerCfg(64, 128)][:L]
+    w = workloads.get("C2")
+    s = Setup(L, H, d, table, workloads.sign_table(17, L, d)).build()
+    k, v = _draw(w, L, B, H, T, d, "bf16", 18)
+    kd, vd = bf16_bits_to_torch(k).cuda(), bf16_bits_to_torch(v).cuda()
+    T_cap = T + 16
+    lay = s.gpu.layout(B, T_cap)
+    cache = torch.full((lay.total_bytes,), 0xAB, dtype=torch.uint8, device="cuda")
+    s.gpu.encode(kd, vd, cache, lay, t_begin=t_begin)
+    bt = 64
+    per = -(-T_cap // bt)
+    play = s.gpu.pool_layout(B * per, bt)
+    pool = torch.zeros((play.total_bytes,), dtype=torch.uint8, device="cuda")
+    order = np.random.default_rng(3).permutation(B * per).astype(np.int32).reshape(B, per)
+    tab = torch.from_numpy(order).cuda()
+    pos = torch.full((B,), t_begin, dtype=torch.int32, device="cuda")
+    s.gpu.encode_paged(kd, vd, pos, tab, pool, play)
+    outs, pouts = {}, {}
+    for dt in (torch.float32, torch.bfloat16):
+        for dst, paged in ((outs, False), (pouts, True)):
+            ko = torch.full((L, B, H, T, d), float("nan"), dtype=dt, device="cuda")
+            vo = torch.full_like(ko, float("nan"))
+            if paged:
+                s.gpu.decode_paged(pool, play, tab, t_begin, t_begin + T, ko, vo)
+            else:
+                s.gpu.decode(cache, lay, t_begin, t_begin + T, ko, vo)
+            dst[dt] = (ko, vo)
+        torch.cuda.synchronize()
+        # the same codes, however they are stored, decode to the same bits
+        for kind in range(2):
+            assert torch.equal(outs[dt][kind].view(torch.uint8), pouts[dt][kind].view(torch.uint8))
+        outs[dt] = tuple(torch_to_np(x) for x in outs[dt])
+    host = torch_to_np(cache)
+    assert untouched_outside(host, s, B, T, T_cap, t_begin, 0xAB)
+    nvec = B * H * T
+    vpw = 64 // (d // 32)
+    rng = np.random.default_rng(4)
+    picks = [(l, kind, j) for l in range(L) for kind in range(2)
+             for j in range(max(0, (nvec - 1) // vpw - 2) * vpw, nvec)]
+    picks += [(int(rng.integers(0, L)), int(rng.integers(0, 2)), int(rng.integers(0, nvec)))
+              for _ in range(600)]
+    chk32, chk16, unflagged, hdr_ulp = DecodeCheck(), DecodeCheck(), 0, 0
+    for l, kind, j in picks:
+        bh, t = divmod(j, T)
+        b, h = divmod(bh, H)
+        x = ((k if kind == 0 else v)[l, b, h, t].astype(np.uint32) << 16).view(np.float32)
+        kd_ = s.orc.kinds[2 * l + kind]
+        ref = oracle.encode_vector(x, s.signs[l], kd_)
+        kg, qg, rn, hg = s.orc.read_vector(host, B, T_cap, l, kind, b, h, t_begin + t)
+        unflagged += int(((kg != ref.k) & ~oracle.angle_flags(ref.u, kd_.n)).sum())
+        unflagged += int(((qg != ref.q) & ~oracle.norm_flags(ref.t, kd_.norm_bits, ref.hdr,
+                                                              kd_.norm_mode)).sum())
+        du = np.abs(hg.view(np.int32).astype(np.int64) - ref.hdr.view(np.int32).astype(np.int64))
+        hdr_ulp = max(hdr_ulp, int(du.max()))
+        dec = oracle.decode_vector(kd_, s.signs[l], kg, qg, rn, hg, "f64")
+        mirror = oracle.decode_vector(kd_, s.signs[l], kg, qg, rn, hg, "f32")
+        check_decoded(chk32, dec[None], d, g32=outs[torch.float32][kind][l, b, h, t][None],
+                      mirror32=mirror[None])
+        check_decoded(chk16, dec[None], d, g16=outs[torch.bfloat16][kind][l, b, h, t][None])
+    _say(f"[n=128 d={d} T={T}] {len(picks)} vectors, fp32 {chk32.line()}; bf16 {chk16.line()}")
+    assert unflagged == 0 and hdr_ulp <= 2      # the bars of the other multi-tile encode tests
+    assert chk32.ok() and chk16.ok()
+
+
 @pytest.mark.parametrize("cfg", ["C2", "C3", "C4"])
 def test_cache_full_size_sampled(gpu, cfg):
     """A benchmark workload at full size in the launch configuration the benchmark times:
