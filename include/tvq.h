@@ -183,17 +183,19 @@ tvq_status tvq_decode(const tvq_codec* c, const void* cache, const tvq_layout* l
  *   t_end      1 .. lay->capacity_tokens tokens attended (slots [0, t_end))
  *   workspace  device scratch of at least tvq_attention_workspace(...) bytes, 16-byte
  *              aligned, owned by the caller; its contents are overwritten
- * The token range is split into equal chunks (whole tile pairs, at least 4 tiles) so that a
- * launch has about one chunk wave per wave slot of the codec's device (its compute units
- * times the resident waves per compute unit of the chunk kernel of the layer's formats, taken
- * at tvq_create); the workspace holds one partial (max, sum, d accumulators) per query head
- * and chunk, so its size depends on the device the codec was created on.
+ * The token range of a (sequence, KV head) is split into spans of whole tiles, one per
+ * workgroup, so that a launch has about as many workgroups as the codec's device holds at once
+ * (its compute units times the resident workgroups of the layer's formats, taken at
+ * tvq_create); the workspace holds one partial (max, sum, d accumulators) per query head and
+ * span.  Its size is that of a split into equal chunks, one per wave slot (whole tile pairs, at
+ * least 4 tiles), which is never fewer than the spans; it depends on the device the codec was
+ * created on.
  * tvq_attention_workspace names no layer and gives the size for the formats with the most
  * chunks, which covers every layer.  Query heads are processed up to 4 per pass over the
  * codes (G > 4 reads them ceil(G/4) times).  Arithmetic is fp32 (expect ~1e-5 relative to an fp64 evaluation).
  * Supported: d = 64 or 128, G <= 64, and for both K and V of the layer n = 64 or 256 with
  * 8-bit linear or 4-bit log-space norms (TVQ_ERR_UNSUPPORTED otherwise).  Launches two
- * kernels on `stream`. */
+ * kernels on `stream`, one where every sequence is a single span. */
 tvq_status tvq_attention_workspace(const tvq_codec* c, int64_t batch, int32_t num_q_heads,
                                    int64_t t_end, int64_t* bytes);
 tvq_status tvq_attention_decode(const tvq_codec* c, const void* cache, const tvq_layout* lay,
@@ -262,7 +264,7 @@ tvq_status tvq_decode_paged(const tvq_codec* c, const void* pool, const tvq_layo
  * <= 0 gives a zero output).  max_ctx (host, 1 .. max_blocks * block_tokens) bounds every
  * context and fixes the launch shape, so the call can be replayed as the lengths grow.  The
  * workspace is at least tvq_attention_paged_workspace(c, batch, num_q_heads, max_ctx,
- * block_tokens) bytes.  Two kernel launches on `stream`. */
+ * block_tokens) bytes.  Kernel launches as tvq_attention_decode. */
 tvq_status tvq_attention_paged_workspace(const tvq_codec* c, int64_t batch, int32_t num_q_heads,
                                          int64_t max_ctx, int64_t block_tokens, int64_t* bytes);
 tvq_status tvq_attention_paged(const tvq_codec* c, const void* pool, const tvq_layout* pool_layout,

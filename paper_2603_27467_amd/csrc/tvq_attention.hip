@@ -12,20 +12,26 @@
 // vector, and every token is read as codes only.  y' is formed exactly as the decode kernels
 // form it (same tables, same fp32 operation order).
 //
-// Split over tokens (split-K): a chunk wave takes `chunk_tokens` tokens of one (sequence, KV
-// head) for up to four of the G query heads (G > 4 runs in passes of balanced size).  The host
-// sizes the chunks so that a launch has about one chunk wave per wave slot of the device.
-//   prologue  q^_g = scale * log2(e) * W D q_g into LDS (the d/32 lanes of vector slot g)
+// Split over tokens (split-K): a workgroup takes a span of whole tiles of one (sequence, KV
+// head) for up to four of the G query heads (G > 4 runs in passes of balanced size), its four
+// waves as even a share each as whole tiles allow.  The spans number about as many as the
+// device holds workgroups, and hold the same number of tiles to within one, also where the
+// contexts differ and are known to the device only (AttnArgs): the launch ends when its longest
+// wave does.  8 sequences of 1025 to 4101 tokens, 8 KV heads, 32 query heads, d = 128: 24 us a
+// layer, 33 us with chunks cut from the longest context (1736 of 4096 waves had work).
+//   prologue  q^_g = scale * log2(e) * W D q_g into LDS, one head per wave; the loads that the
+//             first tile needs are issued before any of them is waited for
 //   per tile  y'_K from the K codes, the scores s_g = q^_g . y'_K, then y'_V from the V codes
 //             and, per head, acc_g += 2^(s_g - m_g) y'_V and l_g += 2^(s_g - m_g)
-//   out       (m, l, acc[d]) per query head and chunk into the workspace
+//   out       the waves' (m, l, acc[d]) summed in LDS, one partial per query head and span into
+//             the workspace; a launch whose sequences are one span each stores its outputs
 // The chunk kernel (attn_mfma_chunk_kernel) does both contractions on the matrix cores, 16
 // tokens (d = 128) or 32 tokens (d = 64) x 4 heads per tile; its layouts are described where
 // it is.
 // m_g is a reference point shared by the wave, not the running maximum: it is raised (and acc,
 // l rescaled) only when a score exceeds it by more than kLazyLog2, so every weight stays below
 // 2^kLazyLog2 and the rescale runs on a few tiles of a chunk.  The merge kernel combines the
-// chunks of each output, M = max m_c, L = sum l_c 2^(m_c - M), A = sum acc_c 2^(m_c - M), and
+// spans of each output, M = max m_c, L = sum l_c 2^(m_c - M), A = sum acc_c 2^(m_c - M), and
 // stores D W (A / L).  The next tile's codes load while the current one is worked on.  All
 // arithmetic is fp32; scores are in log2 units so each weight is one v_exp_f32.
 #include <float.h>
@@ -65,13 +71,80 @@ struct AttnWave {
   static constexpr int LPV = D / kElemsPerLane;
   static constexpr int VPW = kWave / LPV;
   int lane, sub, vslot;
-  uint32_t b, h, chunk, g0, gc;  // query heads g0 .. g0 + gc - 1 of KV head h
-  uint32_t t0, ntok;             // the chunk's tokens [t0, t0 + ntok)
+  uint32_t b, h;                 // sequence and KV head
+  uint32_t t0, ntok;             // the wave's tokens [t0, t0 + ntok)
   uint32_t row;                  // cache slot of token 0 of (b, h) (contiguous layout)
-  uint32_t blk;                  // paged: lane i holds the pool block of the chunk's i-th block
-  SegParams sp[2];               // K and V of the layer
+  uint32_t blk;                  // paged: lane i holds the pool block of the wave's i-th block
   const uint8_t* plane[2][3];
 };
+
+// Inclusive prefix sum over the wave's lanes (row shifts inside the rows of 16, then the last
+// lane of each row or half broadcast to the next; lanes without a source add 0).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
+  return v;
+}
+
+// Context of sequence b: t_end, or its own length clipped to it.
+__device__ __forceinline__ uint32_t seq_context(const AttnArgs& a, uint32_t b) {
+  if (!a.pg.seq) return a.t_end;
+  const int32_t len = a.pg.seq[b];
+  return len <= 0 ? 0u : min((uint32_t)len, a.t_end);
+}
+
+// span_count of AttnArgs for a sequence of T tiles, `total` tiles in all.  T * spare is exact in
+// fp64 (spare is at most the workgroups of a launch), and its quotient cannot round up to an
+// integer above it, so the counts add up to at most n_part.
+__device__ __forceinline__ uint32_t span_count(const AttnArgs& a, uint32_t T, uint32_t total) {
+  const uint32_t c = T <= a.max_span ? 1u : (T + a.max_span - 1) / a.max_span;
+  const uint32_t more = (uint32_t)((double)T * (double)a.spare / (double)total);
+  return max(c, min(c + more, (T + kWavesPerBlock - 1) / kWavesPerBlock));
+}
+
+// Columns [first, first + count) of one sequence.
+struct SeqColumns {
+  uint32_t b, first, count;
+};
+
+// The columns of sequence `want` (BY_SEQ) or of the sequence that holds column `want`; count 0
+// when no sequence does.  Uniform; every lane of the wave takes part.
+template <int D, bool BY_SEQ>
+__device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t want) {
+  constexpr uint32_t VPW = AttnWave<D>::VPW;
+  if (!a.pg.seq) {
+    const uint32_t b = BY_SEQ ? want : want / a.per_seq;
+    return SeqColumns{b, b * a.per_seq, a.per_seq};
+  }
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  uint32_t total = 0;
+  for (uint32_t b0 = 0; b0 < a.B; b0 += kWave) {
+    const uint32_t T = b0 + lane < a.B ? (seq_context(a, b0 + lane) + VPW - 1) / VPW : 0u;
+    total += (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(T), kWave - 1);
+  }
+  total = max(total, 1u);
+  uint32_t off = 0;
+  for (uint32_t b0 = 0; b0 < a.B; b0 += kWave) {
+    const bool in = b0 + lane < a.B;
+    const uint32_t T = in ? (seq_context(a, b0 + lane) + VPW - 1) / VPW : 0u;
+    const uint32_t n = in ? span_count(a, T, total) : 0u;
+    const uint32_t end = off + wave_scan(n);
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(
+        in && (BY_SEQ ? b0 + lane == want : want >= end - n && want < end));
+    if (hit != 0) {
+      const int l = __builtin_ctzll(hit);
+      const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)n, l);
+      return SeqColumns{b0 + (uint32_t)l, (uint32_t)__builtin_amdgcn_readlane((int)end, l) - cnt,
+                        cnt};
+    }
+    off = (uint32_t)__builtin_amdgcn_readlane((int)end, kWave - 1);
+  }
+  return SeqColumns{0, 0, 0};
+}
 
 template <int KW, int KN, int VW, int VN>
 struct TilePair {
@@ -116,98 +189,79 @@ __device__ __forceinline__ TilePair<KW, KN, VW, VN> tile_pair(const AttnArgs& a,
     slot0 = ((blk * a.H + w.h) << a.pg.block_log2) + (tok & ((1u << a.pg.block_log2) - 1u));
   }
   TilePair<KW, KN, VW, VN> p;
-  p.k = load_codes_from<KW, KN>(w.plane[0], w.sp[0].rec, slot0, j, w.sub);
-  p.v = load_codes_from<VW, VN>(w.plane[1], w.sp[1].rec, slot0, j, w.sub);
+  p.k = load_codes_from<KW, KN>(w.plane[0], a.seg[0].rec, slot0, j, w.sub);
+  p.v = load_codes_from<VW, VN>(w.plane[1], a.seg[1].rec, slot0, j, w.sub);
   return p;
 }
 
-// q^_g = scale * log2(e) * W D q_g of the pass's query heads into LDS: head g0 + g on the lanes
-// of vector slot g (the other slots repeat the first head and store nothing).
-template <int D, bool F32Q>
-__device__ __forceinline__ void query_transform(const AttnArgs& a, const AttnWave<D>& w,
-                                                float* qh) {
-  constexpr int LPV = AttnWave<D>::LPV;
-  const uint32_t g = (uint32_t)w.vslot < w.gc ? (uint32_t)w.vslot : 0u;
-  const uint64_t elem = ((uint64_t)w.b * a.Hq + w.h * a.G + w.g0 + g) * D + w.sub * kElemsPerLane;
-  uint32_t sm[16];
-  load_words<16>(a.sign_masks + (size_t)a.layer * (D / 2) + w.sub * 16, sm);
-  float x[kElemsPerLane];
-  if constexpr (F32Q) {
-    uint32_t raw[32];
-    load_words<32>((const uint32_t*)a.q + elem, raw);
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      x[2 * m] = __uint_as_float(raw[2 * m] ^ (sm[m] << 16));
-      x[2 * m + 1] = __uint_as_float(raw[2 * m + 1] ^ (sm[m] & 0x80000000u));
-    }
-  } else {
-    uint32_t raw[16];
-    load_words<16>((const uint32_t*)((const uint16_t*)a.q + elem), raw);
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const uint32_t wv = raw[m] ^ sm[m];
-      x[2 * m] = __uint_as_float(wv << 16);
-      x[2 * m + 1] = __uint_as_float(wv & 0xFFFF0000u);
-    }
+// The Sylvester butterfly of a vector held EPL = D / 64 consecutive elements per lane, stages in
+// ascending order: element bit 0 inside the lane at d = 128, then the stages over the lane's
+// bits, where the lane with the bit clear keeps a + b and its partner a - b.
+template <int EPL>
+__device__ __forceinline__ void fwht_across_lanes(float (&x)[EPL], int lane) {
+  if constexpr (EPL == 2) {
+    const float p = x[0], q = x[1];
+    x[0] = p + q;
+    x[1] = p - q;
   }
-  fwht_in_lane(x);
-  fwht_cross_lane_signed<LPV>(x, w.sub);          // sigma * W D q
-  const float mul = lane_negated<LPV>(w.sub) ? -a.qscale : a.qscale;
-  if ((uint32_t)w.vslot < w.gc) {
-    float* dst = qh + (g * LPV + w.sub) * kQPitch;
 #pragma unroll
-    for (int i = 0; i < kElemsPerLane; i += 4)
-      *(float4*)(dst + i) = make_float4(x[i] * mul, x[i + 1] * mul, x[i + 2] * mul, x[i + 3] * mul);
+  for (int b = 1; b < kWave; b <<= 1) {
+    const float sgn = (lane & b) ? -1.0f : 1.0f;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) x[e] = __builtin_fmaf(x[e], sgn, __shfl_xor(x[e], b));
   }
 }
 
-// The chunk wave's work: (sequence, KV head, chunk, pass of query heads), the chunk's tokens
-// (the sequence's own context with per-sequence lengths) and, for a paged cache, the pool
-// blocks of the chunk (lane i: its i-th block).  A chunk with no token writes partials of
-// weight 0 and returns false, as does a wave past the grid's work.
+// The sign bits of a lane's EPL elements from their word of the layer's masks (bit 15: even
+// elements, bit 31: odd ones).
+template <int EPL>
+__device__ __forceinline__ void apply_signs(float (&x)[EPL], uint32_t smw, int lane) {
+  const uint32_t lo = (smw << 16) & 0x80000000u, hi = smw & 0x80000000u;
+  if constexpr (EPL == 2) {
+    x[0] = __uint_as_float(__float_as_uint(x[0]) ^ lo);
+    x[1] = __uint_as_float(__float_as_uint(x[1]) ^ hi);
+  } else {
+    x[0] = __uint_as_float(__float_as_uint(x[0]) ^ ((lane & 1) ? hi : lo));
+  }
+}
+
+// Elements EPL lane .. of the query vector at element `elem` of q.
 template <int D>
-__device__ __forceinline__ bool chunk_setup(const AttnArgs& a, AttnWave<D>& w, uint32_t wib) {
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + wib);
-  if (wave >= a.B * a.H * a.n_chunks * a.n_pass) return false;
-  const uint32_t pass = wave % a.n_pass;
-  const uint32_t bhc = wave / a.n_pass;
-  const uint32_t bh = bhc / a.n_chunks;
-  w.chunk = bhc - bh * a.n_chunks;
-  w.b = bh / a.H;
-  w.h = bh - w.b * a.H;
-  w.g0 = pass * a.pass_heads;
-  w.gc = min(a.pass_heads, a.G - w.g0);
-  w.t0 = w.chunk * a.chunk_tokens;
-  // the sequence's context: t_end, or its own length (paged), at most what its table covers
-  uint32_t ctx = a.t_end;
-  if (a.pg.seq) {
-    const int32_t len = a.pg.seq[w.b];
-    ctx = len <= 0 ? 0u : min((uint32_t)len, a.t_end);
+__device__ __forceinline__ void load_query(const AttnArgs& a, uint64_t elem, int lane,
+                                           float (&x)[D / kWave]) {
+  constexpr int EPL = D / kWave;
+  if (a.q_f32) {
+    const float* p = (const float*)a.q + elem + EPL * lane;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) x[e] = p[e];
+  } else if constexpr (EPL == 2) {
+    const uint32_t v = *(const uint32_t*)((const uint16_t*)a.q + elem + 2 * lane);
+    x[0] = __uint_as_float(v << 16);
+    x[1] = __uint_as_float(v & 0xFFFF0000u);
+  } else {
+    x[0] = __uint_as_float((uint32_t)((const uint16_t*)a.q)[elem + lane] << 16);
   }
-  if (w.t0 >= ctx) {
-    // nothing to attend in this chunk: a partial of weight 0 for the merge
-    for (uint32_t g = 0; g < w.gc; ++g) {
-      const uint64_t idx = ((uint64_t)w.b * a.Hq + w.h * a.G + w.g0 + g) * a.n_chunks + w.chunk;
-      if (w.lane < D / 4)
-        *(float4*)(a.ws_acc + idx * D + 4 * w.lane) = make_float4(0, 0, 0, 0);
-      if (w.lane == 0) *(float2*)(a.ws_ml + idx * 2) = make_float2(-INFINITY, 0.0f);
-    }
-    return false;
+}
+
+// o = D W (A / L) of output j, its elements EPL lane .. on the lanes; no token at all (M = -inf)
+// gives zeros.
+template <int D>
+__device__ __forceinline__ void store_output(const AttnArgs& a, uint64_t j, float (&x)[D / kWave],
+                                             float M, float L, uint32_t smw, int lane) {
+  constexpr int EPL = D / kWave;
+  const float inv = M == -INFINITY ? 0.0f : 1.0f / L;
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) x[e] *= inv;
+  fwht_across_lanes<EPL>(x, lane);
+  apply_signs<EPL>(x, smw, lane);
+  const uint64_t elem = j * D + EPL * lane;
+  if constexpr (EPL == 2) {
+    if (a.o_f32) *(float2*)((float*)a.o + elem) = make_float2(x[0], x[1]);
+    else *(uint32_t*)((uint16_t*)a.o + elem) = bf16x2_rne(x[0], x[1]);
+  } else {
+    if (a.o_f32) ((float*)a.o)[elem] = x[0];
+    else ((uint16_t*)a.o)[elem] = (uint16_t)(bf16x2_rne(x[0], 0.0f) & 0xFFFFu);
   }
-  w.ntok = min(a.chunk_tokens, ctx - w.t0);
-  w.row = bh * a.cap;
-  w.blk = 0;
-  if (a.pg.table) {
-    // lane i: the pool block of the chunk's i-th block (entries past the table or naming no
-    // pool block read block 0, so a corrupt table stays inside the pool)
-    const uint32_t i = (w.t0 >> a.pg.block_log2) + (uint32_t)w.lane;
-    const uint32_t blk = i < a.pg.max_blocks
-                             ? (uint32_t)a.pg.table[(size_t)w.b * a.pg.max_blocks + i] : 0u;
-    w.blk = blk < a.pg.n_blocks ? blk : 0u;
-  }
-  for (int kind = 0; kind < 2; ++kind)
-    for (int p = 0; p < 3; ++p) w.plane[kind][p] = a.cache + a.n_slots * w.sp[kind].pre[p];
-  return true;
 }
 
 // The chunk kernel, with the two contractions on the matrix cores (v_mfma_f32_4x4x1f32: 16
@@ -324,52 +378,103 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   __shared__ float2 s_lut_k[1 << KW];
   __shared__ float2 s_lut_v[kShared ? 1 : (1 << VW)];
   __shared__ __attribute__((aligned(16))) float s_wave[kWavesPerBlock][kStageWordsOf<D>];
-  const SegParams spk = a.segs[2 * a.layer], spv = a.segs[2 * a.layer + 1];
-  for (uint32_t e = threadIdx.x; e < (1u << KW); e += kBlockThreads)
-    s_lut_k[e] = ((const float2*)a.lut)[spk.lut_off + e];
-  if constexpr (!kShared) {
-    for (uint32_t e = threadIdx.x; e < (1u << VW); e += kBlockThreads)
-      s_lut_v[e] = ((const float2*)a.lut)[spv.lut_off + e];
-  }
-  const float2* const lut_v = kShared ? s_lut_k : s_lut_v;
-  __syncthreads();
-
-  const uint32_t wib = threadIdx.x / kWave;
+  __builtin_amdgcn_s_setprio(3);
+  const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x & (kWave - 1);
+  // the workgroup's column, KV head and pass.  The passes of one span read the same codes: they
+  // are 8 workgroups apart, on the same XCD (workgroups go round the 8 XCDs), so the later ones
+  // find them in its L2.
+  const uint32_t q8 = blockIdx.x >> 3;
+  const uint32_t pass = q8 % a.n_pass;
+  const uint32_t unit = (q8 / a.n_pass) * 8 + (blockIdx.x & 7u);
+  if (unit >= a.n_part * a.H) return;
   AttnWave<D> w;
   w.lane = lane;
-  w.sp[0] = spk;
-  w.sp[1] = spv;
-  if (!chunk_setup<D>(a, w, wib)) return;
+  w.h = unit / a.n_part;
+  const uint32_t col = unit - w.h * a.n_part;
+  const SeqColumns sc = seq_columns<D, false>(a, col);
+  if (sc.count == 0) return;
+  w.b = sc.b;
+  // the span's tiles, then the wave's: as even as whole tiles allow
+  const uint32_t ctx = seq_context(a, w.b);
+  const uint32_t tiles = (ctx + VPW - 1) / VPW;
+  const uint32_t k = col - sc.first;
+  const uint32_t per = tiles / sc.count, extra = tiles - per * sc.count;
+  const uint32_t span0 = k * per + min(k, extra), span = per + (k < extra ? 1u : 0u);
+  const uint32_t wper = span / kWavesPerBlock, wextra = span % kWavesPerBlock;
+  const uint32_t nt = wper + (wib < wextra ? 1u : 0u);
+  w.t0 = nt != 0 ? (span0 + wib * wper + min(wib, wextra)) * VPW : 0u;
+  w.ntok = nt != 0 ? min(nt * VPW, ctx - w.t0) : 1u;   // no tile: token 0 is loaded, not used
+  w.row = (w.b * a.H + w.h) * a.cap;
+  w.blk = 0;
+  if (a.pg.table) {
+    // lane i: the pool block of the wave's i-th block (entries past the table or naming no
+    // pool block read block 0, so a corrupt table stays inside the pool)
+    const uint32_t i = (w.t0 >> a.pg.block_log2) + (uint32_t)lane;
+    const uint32_t blk = i < a.pg.max_blocks
+                             ? (uint32_t)a.pg.table[(size_t)w.b * a.pg.max_blocks + i] : 0u;
+    w.blk = blk < a.pg.n_blocks ? blk : 0u;
+  }
+  for (int kind = 0; kind < 2; ++kind)
+    for (int p = 0; p < 3; ++p) w.plane[kind][p] = a.cache + a.n_slots * a.seg[kind].pre[p];
+  const uint32_t g0 = pass * a.pass_heads;
+  const uint32_t gc = min(a.pass_heads, a.G - g0);     // query heads g0 .. g0 + gc - 1
   float* const lds = s_wave[wib];
 
-  // q^ of the pass's heads: computed in the layout of vector slot g = head g, read back as
-  // head x on the lane's slice (zero for heads past the pass)
-  {
-    AttnWave<D> wq = w;
-    wq.sub = lane % LPV;
-    wq.vslot = lane / LPV;
-    if (a.q_f32) query_transform<D, true>(a, wq, lds);
-    else query_transform<D, false>(a, wq, lds);
-  }
-  wave_lds_sync();
   // the code layout: token tok of the tile on slice sl (tile loads and both rebuilds use it)
   const int x = lane & 3, c = (lane >> 2) & 3, R = lane >> 4;
   const int sl = D == 128 ? c : c >> 1;
   const int tok = D == 128 ? 4 * R + x : 8 * R + 4 * (c & 1) + x;
+  w.sub = sl;
+  w.vslot = tok;
+  const uint32_t last = nt != 0 ? nt - 1 : 0u;
+
+  // everything the first tile needs is requested before any of it is used: the query head of
+  // this wave, the tables, the first tile's codes and the first V headers
+  constexpr int EPL = D / kWave;
+  const uint64_t head = (uint64_t)w.b * a.Hq + w.h * a.G + g0 + (wib < gc ? wib : 0u);
+  const uint32_t smw = a.sign_masks[(size_t)a.layer * (D / 2) + (EPL * lane) / 2];
+  float qx[EPL];
+  load_query<D>(a, head * D, lane, qx);
+  const uint32_t ek = threadIdx.x & ((1u << KW) - 1u), ev = threadIdx.x & ((1u << VW) - 1u);
+  const float2 tk = ((const float2*)a.lut)[a.seg[0].lut_off + ek];
+  float2 tv;
+  if constexpr (!kShared) tv = ((const float2*)a.lut)[a.seg[1].lut_off + ev];
+  // log-space V norms: the ladder ratio of each token, computed for LPV tiles at once (the LPV
+  // lanes of a token would otherwise compute the same one): the lane on slice sl holds that of
+  // its token in tile LPV k + sl, and tile LPV k + u reads it from the lane of slice u
+  double vrho = 1.0;
+  u32x2 vh = {0u, 0u};
+  if constexpr (VN != 8) vh = v_header<D>(a, w, min((uint32_t)sl, last));
+  TilePair<KW, KN, VW, VN> ca = tile_pair<D, KW, KN, VW, VN>(a, w, 0);
+
+  // q^_g = scale * log2(e) * W D q_g of the pass's heads, head g0 + i by wave i, into every
+  // wave's LDS; the tables, the same for the workgroup
+  apply_signs<EPL>(qx, smw, lane);
+  fwht_across_lanes<EPL>(qx, lane);
+  s_lut_k[ek] = tk;                              // lanes past the table store its values again
+  if constexpr (!kShared) s_lut_v[ev] = tv;
+  if (wib < gc) {
+    const int e0 = EPL * lane;                   // slice e0 / 32, element e0 % 32 of it
+    const int at = (wib * LPV + e0 / kElemsPerLane) * kQPitch + e0 % kElemsPerLane;
+#pragma unroll
+    for (int v = 0; v < kWavesPerBlock; ++v)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) s_wave[v][at + e] = qx[e] * a.qscale;
+  }
+  const float2* const lut_v = kShared ? s_lut_k : s_lut_v;
+  __syncthreads();
   // q^ is the same on the four rows, so each row keeps a quarter of it: lane (R, c, x) holds
   // elements 32 sl + 8R .. 32 sl + 8R + 7 of head x, and the product over element n takes its
   // B operand from row n / 8 (the lane-group broadcast of the matrix instruction, blgp 4 + n / 8)
   float qr[8];
 #pragma unroll
   for (int i = 0; i < 8; i += 4) {
-    const float4 v = (uint32_t)x < w.gc
+    const float4 v = (uint32_t)x < gc
                          ? *(const float4*)(lds + (x * LPV + sl) * kQPitch + 8 * R + i)
                          : make_float4(0, 0, 0, 0);
     qr[i] = v.x, qr[i + 1] = v.y, qr[i + 2] = v.z, qr[i + 3] = v.w;
   }
-  w.sub = sl;
-  w.vslot = tok;
   // level q of the lane's token at + 32 q (d = 128: two copies, read by even and odd columns)
   const float* const lvl_v = lds + (D == 128 ? 2 * tok + (c & 1) : tok);
   const float* const lvl_k = lvl_v + kLvlWords;
@@ -393,14 +498,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   v4f acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
   constexpr uint32_t kKLevels = (1u << KN) - 1u, kVLevels = (1u << VN) - 1u;
 
-  const uint32_t last = (w.ntok + VPW - 1) / VPW - 1;
   const bool ragged = (w.ntok & (VPW - 1)) != 0;
-  // log-space V norms: the ladder ratio of each token, computed for LPV tiles at once (the LPV
-  // lanes of a token would otherwise compute the same one): the lane on slice sl holds that of
-  // its token in tile LPV k + sl, and tile LPV k + u reads it from the lane of slice u
-  double vrho = 1.0;
-  u32x2 vh = {0u, 0u};
-  if constexpr (VN != 8) vh = v_header<D>(a, w, min((uint32_t)sl, last));
   auto tile_work = [&](const TilePair<KW, KN, VW, VN>& cd, uint32_t tile) {
     // ---- scores: y'_K on this lane's slice, 32 matrix products over the slice ----
     v4f sc = {0, 0, 0, 0};
@@ -548,9 +646,16 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   };
 
   // tiles two at a time from two code buffers: each tile's codes load while the one before
-  // it is worked on
-  TilePair<KW, KN, VW, VN> ca = tile_pair<D, KW, KN, VW, VN>(a, w, 0);
-  for (uint32_t t = 0; t <= last; t += 2) {
+  // it is worked on.  The SIMD issues for its oldest wave first, so of four waves with the same
+  // work the oldest would end far ahead of the youngest and the launch would finish at a falling
+  // occupancy; a wave therefore lowers its priority as it gets on (5/8, 27/32 and 15/16 of its
+  // tiles), which lets the others catch up.  16 sequences of 32,770 tokens, one layer: the waves
+  // ended between 168 and 285 us, with it between 207 and 262 us.
+  const uint32_t mark1 = (nt * 5 / 8) & ~1u, mark2 = (nt * 27 / 32) & ~1u, mark3 = (nt * 15 / 16) & ~1u;
+  for (uint32_t t = 0; t < nt; t += 2) {
+    if (t == mark1) __builtin_amdgcn_s_setprio(2);
+    if (t == mark2) __builtin_amdgcn_s_setprio(1);
+    if (t == mark3) __builtin_amdgcn_s_setprio(0);
     const uint32_t t1 = min(t + 1, last);
     const TilePair<KW, KN, VW, VN> cb = tile_pair<D, KW, KN, VW, VN>(a, w, t1);
     tile_work(ca, t);
@@ -559,44 +664,73 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   }
 
   // l of head x: the rows hold different tokens, and so do the columns c and c + 1 at d = 64
-  // (the other columns of a row hold the same sums); lane 4b + j stores elements 8b .. 8b + 7
-  // (d = 128) or 4b .. 4b + 3 (d = 64) of head j
+  // (the other columns of a row hold the same sums)
   if constexpr (D == 64) lsum += __shfl_xor(lsum, 4);
   lsum += __shfl_xor(lsum, 16);
   lsum += __shfl_xor(lsum, 32);
-  if ((uint32_t)x < w.gc) {
-    const uint64_t idx = ((uint64_t)w.b * a.Hq + w.h * a.G + w.g0 + x) * a.n_chunks + w.chunk;
-    if constexpr (D == 128) {
-      float* dst = a.ws_acc + idx * D + 8 * (lane >> 2);
-      *(float4*)dst = make_float4(acc0[0], acc1[0], acc0[1], acc1[1]);
-      *(float4*)(dst + 4) = make_float4(acc0[2], acc1[2], acc0[3], acc1[3]);
-    } else {
-      *(float4*)(a.ws_acc + idx * D + 4 * (lane >> 2)) =
-          make_float4(acc0[0], acc0[1], acc0[2], acc0[3]);
-    }
-    if (lane < 4) *(float2*)(a.ws_ml + idx * 2) = make_float2(m, lsum);
+  // the four waves' partials through LDS: lane 4b + j writes elements 8b .. 8b + 7 (d = 128) or
+  // 4b .. 4b + 3 (d = 64) of head j, then wave i sums head i over the waves in wave order
+  constexpr int kAccPitch = D + 4;
+  constexpr int kMl = kAttnPassHeads * kAccPitch;
+  static_assert(kMl + 2 * kAttnPassHeads <= kStageWordsOf<D>, "the partials fit the staging");
+  wave_lds_sync();                             // the last tile's staging reads are done
+  if constexpr (D == 128) {
+    float* dst = lds + x * kAccPitch + 8 * (lane >> 2);
+    *(float4*)dst = make_float4(acc0[0], acc1[0], acc0[1], acc1[1]);
+    *(float4*)(dst + 4) = make_float4(acc0[2], acc1[2], acc0[3], acc1[3]);
+  } else {
+    *(float4*)(lds + x * kAccPitch + 4 * (lane >> 2)) =
+        make_float4(acc0[0], acc0[1], acc0[2], acc0[3]);
   }
+  if (lane < 4) *(float2*)(lds + kMl + 2 * x) = make_float2(m, lsum);
+  __syncthreads();
+  if (wib >= gc) return;
+  float M = -INFINITY;
+#pragma unroll
+  for (int v = 0; v < kWavesPerBlock; ++v) M = fmaxf(M, s_wave[v][kMl + 2 * wib]);
+  float L = 0.0f, ax[EPL];
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) ax[e] = 0.0f;
+#pragma unroll
+  for (int v = 0; v < kWavesPerBlock; ++v) {
+    const float mv = s_wave[v][kMl + 2 * wib];
+    const float f = mv == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mv - M);
+    L = __builtin_fmaf(s_wave[v][kMl + 2 * wib + 1], f, L);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e)
+      ax[e] = __builtin_fmaf(s_wave[v][wib * kAccPitch + EPL * lane + e], f, ax[e]);
+  }
+  if (a.direct) {
+    const uint32_t smo = a.sign_masks[(size_t)a.layer * (D / 2) + (EPL * lane) / 2];
+    store_output<D>(a, head, ax, M, L, smo, lane);
+    return;
+  }
+  const uint64_t idx = (uint64_t)(w.h * a.G + g0 + wib) * a.n_part + col;
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) a.ws_acc[idx * D + EPL * lane + e] = ax[e];
+  if (lane == 0) *(float2*)(a.ws_ml + idx * 2) = make_float2(M, L);
 }
 
 // One output per wave, its elements across the lanes: lane l keeps elements EPL l .. EPL l +
-// EPL - 1 (EPL = d / 64) of A = sum_c acc_c 2^(m_c - M), so the chunks' partials are read as
-// contiguous rows and summed without any exchange between lanes.  The chunks' (m_c, l_c) are
+// EPL - 1 (EPL = d / 64) of A = sum_c acc_c 2^(m_c - M), so the spans' partials are read as
+// contiguous rows and summed without any exchange between lanes.  The spans' (m_c, l_c) are
 // read 64 at a time, one per lane: M = max m_c, then the weights 2^(m_c - M), L, and each
-// chunk's weight taken from its lane by a scalar read.  o = D W (A / L): the butterfly's
-// stages over element bits that lie across lanes are exchanges with the partner lane.
-template <int D, bool F32OUT>
+// span's weight taken from its lane by a scalar read.  o = D W (A / L).
+template <int D>
 __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
   constexpr int EPL = D / kWave;                      // elements per lane: 1 or 2
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t j = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock +
                                                      threadIdx.x / kWave);
   if (j >= a.B * a.Hq) return;
-  const uint32_t nc = a.n_chunks;
-  const float2* const ml = (const float2*)(a.ws_ml + (size_t)j * nc * 2);
-  const float* const acc = a.ws_acc + (size_t)j * nc * D + EPL * lane;
-  // the sign bits of the lane's elements: word e / 2 of the layer's masks, bit 15 or 31
+  const uint32_t b = j / a.Hq;
+  const SeqColumns sc = seq_columns<D, true>(a, b);
+  const uint32_t nc = sc.count;
+  const uint64_t col0 = (uint64_t)(j - b * a.Hq) * a.n_part + sc.first;
+  const float2* const ml = (const float2*)(a.ws_ml + col0 * 2);
+  const float* const acc = a.ws_acc + col0 * D + EPL * lane;
   const uint32_t smw = a.sign_masks[(size_t)a.layer * (D / 2) + (EPL * lane) / 2];
-  // M over every chunk (an empty chunk carries m = -inf)
+  // M over every span (an empty one carries m = -inf)
   float M = -INFINITY;
   for (uint32_t c = (uint32_t)lane; c < nc; c += kWave) M = fmaxf(M, ml[c].x);
   M = wave_max(M);
@@ -611,7 +745,7 @@ __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
       const float wc = v.x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(v.x - M);
       L = __builtin_fmaf(v.y, wc, L);
       const uint32_t n = min(nc - c0, (uint32_t)kWave);
-      // eight chunks' rows requested before any is used
+      // eight spans' rows requested before any is used
       for (uint32_t k0 = 0; k0 < n; k0 += 8) {
         float r[8][EPL];
 #pragma unroll
@@ -627,7 +761,7 @@ __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
         }
 #pragma unroll
         for (uint32_t k = 0; k < 8; ++k) {
-          // chunk c0 + k0 + k's weight, from its lane (a wave-uniform index below 64)
+          // span c0 + k0 + k's weight, from its lane (a wave-uniform index below 64)
           const int wk = __builtin_amdgcn_readlane(__float_as_int(wc), (int)min(k0 + k, 63u));
           const float wf = k0 + k < n ? __int_as_float(wk) : 0.0f;
 #pragma unroll
@@ -636,39 +770,9 @@ __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
       }
     }
   }
-  // L over the lanes; no token at all (M = -inf) gives zeros
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) L += __shfl_xor(L, o);
-  const float inv = M == -INFINITY ? 0.0f : 1.0f / L;
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) x[e] *= inv;
-  // W: the stage over element bit 0 inside the lane at d = 128, then the stages over the
-  // lane's bits: the lane with the bit clear keeps a + b, its partner a - b
-  if constexpr (EPL == 2) {
-    const float p = x[0], q = x[1];
-    x[0] = p + q;
-    x[1] = p - q;
-  }
-#pragma unroll
-  for (int b = 1; b < kWave; b <<= 1) {
-    const float sgn = (lane & b) ? -1.0f : 1.0f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) x[e] = __builtin_fmaf(x[e], sgn, __shfl_xor(x[e], b));
-  }
-  // D, then the store
-  const uint64_t elem = (uint64_t)j * D + EPL * lane;
-  if constexpr (EPL == 2) {
-    const uint32_t lo = (smw << 16) & 0x80000000u, hi = smw & 0x80000000u;
-    const float o0 = __uint_as_float(__float_as_uint(x[0]) ^ lo);
-    const float o1 = __uint_as_float(__float_as_uint(x[1]) ^ hi);
-    if constexpr (F32OUT) *(float2*)((float*)a.o + elem) = make_float2(o0, o1);
-    else *(uint32_t*)((uint16_t*)a.o + elem) = bf16x2_rne(o0, o1);
-  } else {
-    const uint32_t sb = (lane & 1) ? (smw & 0x80000000u) : ((smw << 16) & 0x80000000u);
-    const float o0 = __uint_as_float(__float_as_uint(x[0]) ^ sb);
-    if constexpr (F32OUT) ((float*)a.o)[elem] = o0;
-    else ((uint16_t*)a.o)[elem] = (uint16_t)(bf16x2_rne(o0, 0.0f) & 0xFFFFu);
-  }
+  store_output<D>(a, j, x, M, L, smw, lane);
 }
 
 template <int D, int KW, int KN, int VW, int VN>
@@ -734,11 +838,12 @@ int tvq_attention_blocks_per_cu(int d, int k_format, int v_format) {
   return nb > 0 ? nb : -1;
 }
 
-int tvq_launch_attention(const tvq::AttnArgs& a, int d, int k_format, int v_format, int o_f32,
+int tvq_launch_attention(const tvq::AttnArgs& a, int d, int k_format, int v_format,
                          void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  const uint64_t chunk_waves = (uint64_t)a.B * a.H * a.n_chunks * a.n_pass;
-  const dim3 grid1((unsigned)((chunk_waves + tvq::kWavesPerBlock - 1) / tvq::kWavesPerBlock));
+  // units (KV head, column) go round the XCDs in eights, the passes of one eight in turn
+  const uint64_t units = (uint64_t)a.H * a.n_part;
+  const dim3 grid1((unsigned)((units + 7) / 8 * 8 * a.n_pass));
   const uint64_t merge_waves = (uint64_t)a.B * a.Hq;
   const dim3 grid2((unsigned)((merge_waves + tvq::kWavesPerBlock - 1) / tvq::kWavesPerBlock));
   const dim3 block(tvq::kBlockThreads);
@@ -746,12 +851,8 @@ int tvq_launch_attention(const tvq::AttnArgs& a, int d, int k_format, int v_form
   else if (d == 64) tvq::launch_chunk_kv<64>(a, k_format, v_format, grid1, s);
   else return -1;
   if (hipGetLastError() != hipSuccess) return -2;
-  if (d == 128) {
-    if (o_f32) hipLaunchKernelGGL((tvq::attn_merge_kernel<128, true>), grid2, block, 0, s, a);
-    else hipLaunchKernelGGL((tvq::attn_merge_kernel<128, false>), grid2, block, 0, s, a);
-  } else {
-    if (o_f32) hipLaunchKernelGGL((tvq::attn_merge_kernel<64, true>), grid2, block, 0, s, a);
-    else hipLaunchKernelGGL((tvq::attn_merge_kernel<64, false>), grid2, block, 0, s, a);
-  }
+  if (a.direct) return 0;
+  if (d == 128) hipLaunchKernelGGL(tvq::attn_merge_kernel<128>, grid2, block, 0, s, a);
+  else hipLaunchKernelGGL(tvq::attn_merge_kernel<64>, grid2, block, 0, s, a);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }

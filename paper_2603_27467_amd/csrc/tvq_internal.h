@@ -108,35 +108,47 @@ struct DecodeArgs {
 };
 
 // Attention of one query token per sequence over one layer of the cache (tvq_attention_decode).
-// Query heads are grouped over the KV heads: query head h*G + g uses KV head h.  A chunk wave
-// covers `chunk_tokens` tokens of one (batch, KV head) for all G query heads and writes, per
-// query head, the running maximum m (log2 units), the sum l of 2^(s - m) and the accumulated
-// rotated-domain value vector acc[d]; the merge kernel combines the chunks.
+// Query heads are grouped over the KV heads: query head h*G + g uses KV head h.  A workgroup
+// covers a span of whole tiles of one (sequence, KV head) for up to kAttnPassHeads query heads
+// and writes, per query head, one partial: the running maximum m (log2 units), the sum l of
+// 2^(s - m) and the accumulated rotated-domain value vector acc[d]; the merge kernel combines
+// the spans of a sequence.
+//
+// The spans of the sequences are the n_part columns of one list per head: sequence b holds
+// span_count(T_b) consecutive columns, T_b its tiles, in batch order.  With every context equal
+// (pg.seq null) that is per_seq columns each; otherwise the contexts are device data and every
+// workgroup counts the same way:
+//   span_count(T) = c(T) + floor(T * spare / sum_b T_b),   c(T) = max(1, ceil(T / max_span)),
+// at most ceil(T / 4) (a tile per wave) where that is at least c(T), with spare = n_part - B c(T
+// of t_end).  The counts never add up to more than n_part, the spans hold close to the same
+// number of tiles whatever the contexts, and equal contexts share the columns evenly.
 struct AttnArgs {
   const uint8_t* cache;
   int64_t n_slots;       // B * H * capacity
   uint32_t cap;
-  const SegParams* segs;
+  SegParams seg[2];      // K and V of the layer
   const uint32_t* sign_masks;
   const float* lut;      // float2 entries, 1/sqrt(d) folded in
   const void* q;         // [B][Hq][d]
   void* o;               // [B][Hq][d]
-  float* ws_acc;         // [B*Hq][n_chunks][d]
-  float* ws_ml;          // [B*Hq][n_chunks][2]
+  float* ws_acc;         // [Hq][n_part][d]
+  float* ws_ml;          // [Hq][n_part][2]
   uint32_t layer, B, H, G, Hq;
-  uint32_t t_end, chunk_tokens, n_chunks;
-  uint32_t pass_heads, n_pass;  // query heads per chunk wave (<= kAttnPassHeads), passes over G
+  uint32_t t_end;
+  uint32_t n_part;       // columns of partials per query head
+  uint32_t per_seq;      // columns of each sequence (pg.seq null)
+  uint32_t spare;        // columns shared by context length (pg.seq not null)
+  uint32_t max_span;     // most tiles of a workgroup's span
+  uint32_t pass_heads, n_pass;  // query heads per workgroup (<= kAttnPassHeads), passes over G
+  uint32_t direct;       // every sequence holds one column: the workgroups store the outputs
   uint32_t q_f32;        // query dtype: 1 = fp32, 0 = bf16
+  uint32_t o_f32;        // output dtype, likewise
   float qscale;          // scale * log2(e): scores in log2 units
   Paging pg;             // pg.seq: context length per sequence (nullptr: t_end for all)
 };
 
 constexpr int kAttnPassHeads = 4;           // accumulators of 4 query heads per wave
 constexpr uint32_t kAttnMaxGroup = 64;      // query heads per KV head
-// The token split gives a launch about kAttnRounds times as many chunk waves as the device
-// holds at once, so that every wave slot stays busy until the launch's end.
-constexpr int64_t kAttnRounds = 1;
-
 // Formats of the attention kernels and of the matrix-core encode: n = 64 or 256 (6- or 8-bit
 // angle codes, every code a valid bin) with 8-bit linear or 4-bit log-space norms.
 inline bool attn_format(uint32_t n, uint32_t mode, uint32_t bits) {
@@ -180,7 +192,7 @@ int tvq_launch_encode(const tvq::EncodeArgs& a, int d, int in_f32, bool fast, un
 int tvq_launch_decode(const tvq::DecodeArgs& a, int d, int out_f32, bool fast, unsigned grid,
                       void* stream);
 // k_format / v_format: bit 0 set for 8-bit angle codes (n = 256), bit 1 for 4-bit log norms.
-int tvq_launch_attention(const tvq::AttnArgs& a, int d, int k_format, int v_format, int o_f32,
+int tvq_launch_attention(const tvq::AttnArgs& a, int d, int k_format, int v_format,
                          void* stream);
 // Chunk-kernel workgroups of head dimension d and the given key and value formats (as for
 // tvq_launch_attention) that one compute unit holds at once, or -1 on a HIP error.
