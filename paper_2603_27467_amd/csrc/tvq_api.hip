@@ -205,9 +205,8 @@ bool desc_valid(const tvq_codec* c, const tvq_tensor_desc* t, int elem_bytes) {
   return true;
 }
 
-unsigned plan_grid(uint32_t nvec, uint32_t vpw, uint32_t num_segs, uint32_t* waves_per_seg,
+unsigned plan_grid(uint64_t tiles_per_seg, uint32_t num_segs, uint32_t* waves_per_seg,
                    uint32_t* tiles_per_wave, uint32_t max_tiles_per_wave) {
-  const uint64_t tiles_per_seg = (nvec + vpw - 1) / vpw;
   const uint64_t total_tiles = tiles_per_seg * num_segs;
   // aim for at least ~32 waves per compute unit of a 256-CU part before grouping tiles
   uint64_t tpw = total_tiles / (256ull * 32ull);
@@ -218,6 +217,30 @@ unsigned plan_grid(uint32_t nvec, uint32_t vpw, uint32_t num_segs, uint32_t* wav
   *tiles_per_wave = (uint32_t)tpw;
   const uint64_t waves = wps * num_segs;
   return (unsigned)((waves + tvq::kWavesPerBlock - 1) / tvq::kWavesPerBlock);
+}
+
+// Grid of an encode or decode launch and its tiles per segment and wave.  Row tiles (row_tiles)
+// where `row_ok` (the lanes' offsets inside a tile fit 32 bits) and the launch has several tiles
+// per wave; `span` positions of a row are cut into tiles (its tokens, and those before them from
+// a tile boundary on).
+template <class Args>
+unsigned plan_tiles(Args& a, bool row_ok, uint64_t rows, uint64_t tokens, uint64_t span,
+                           uint32_t vpw, uint32_t max_tiles_per_wave) {
+  const uint64_t per_row = (span + vpw - 1) / vpw;
+  a.rows = 0;
+  if (row_ok && tvq::row_tiles(tokens, per_row, vpw, a.pg.table != nullptr)) {
+    const unsigned grid = plan_grid(rows * per_row, a.num_segs, &a.waves_per_seg,
+                                    &a.tiles_per_wave, max_tiles_per_wave);
+    if (a.tiles_per_wave > 1) {
+      a.rows = 1;
+      a.div_r = make_div((uint32_t)per_row);
+      a.seg_tiles = (uint32_t)(rows * per_row);
+      return grid;
+    }
+  }
+  a.seg_tiles = (uint32_t)((a.nvec + (uint64_t)vpw - 1) / vpw);
+  return plan_grid(a.seg_tiles, a.num_segs, &a.waves_per_seg, &a.tiles_per_wave,
+                   max_tiles_per_wave);
 }
 
 // cos and sin of 2 pi k / n in fp64: 4k = quarter*n + rem, the angle (pi/2)*rem/n is at most
@@ -590,8 +613,9 @@ static tvq_status encode_launch(const tvq_codec* c, tvq::EncodeArgs& a, const tv
     a.seg_list = c->d_seg_lists + l.first;
     a.num_segs = l.count;
     a.has_n128 = l.fast && l.count > c->n_mfma ? 1u : 0u;
-    const unsigned grid = plan_grid(a.nvec, vpw, a.num_segs, &a.waves_per_seg, &a.tiles_per_wave,
-                                    l.tpw);
+    const unsigned grid = plan_tiles(
+        a, l.fast && !a.mfma_front && (uint64_t)a.stride_t * vpw * 2u < (1ull << 31),
+        (uint64_t)(in->batch * c->H), (uint64_t)in->tokens, (uint64_t)in->tokens, vpw, l.tpw);
     const int rc = tvq_launch_encode(a, c->d, f32, l.fast, grid, stream);
     if (rc == -1) return TVQ_ERR_UNSUPPORTED;
     if (rc != 0) return TVQ_ERR_HIP;
@@ -599,7 +623,7 @@ static tvq_status encode_launch(const tvq_codec* c, tvq::EncodeArgs& a, const tv
   return TVQ_OK;
 }
 
-// Ranges of at least this many vectors per kind whose token count is not a multiple of the
+// Contiguous ranges of at least this many vectors per kind whose token count is not a multiple of the
 // tile's are encoded or decoded in two parts (whole tiles per (batch, head) row, on the
 // kernels that keep a tile's position in scalar registers, then the remaining tokens of every
 // row): below it the extra launch costs more than those kernels save.
@@ -715,6 +739,7 @@ static tvq_status decode_launch(const tvq_codec* c, tvq::DecodeArgs& a,
   a.H = (uint32_t)c->H;
   a.nvec = (uint32_t)(out->batch * c->H * out->tokens);
   const uint32_t vpw = tvq::kWave / (c->d / tvq::kElemsPerLane);
+  a.pos0 = a.pg.table ? a.t_begin & ~(vpw - 1u) : a.t_begin;
   // the common formats go to the multi-tile kernel (a paged source through its block
   // table), the rest to the generic one
   const uint32_t n_fast = c->n_fast;
@@ -725,8 +750,10 @@ static tvq_status decode_launch(const tvq_codec* c, tvq::DecodeArgs& a,
     if (l.count == 0) continue;
     a.seg_list = c->d_seg_lists + l.first;
     a.num_segs = l.count;
-    const unsigned grid = plan_grid(a.nvec, vpw, a.num_segs, &a.waves_per_seg, &a.tiles_per_wave,
-                                    l.tpw);
+    const unsigned grid = plan_tiles(
+        a, l.fast && (uint64_t)a.stride_t * vpw * (out_dtype == TVQ_F32 ? 4u : 2u) < (1ull << 31),
+        (uint64_t)(out->batch * c->H), (uint64_t)out->tokens,
+        (uint64_t)out->tokens + (a.t_begin - a.pos0), vpw, l.tpw);
     const int rc = tvq_launch_decode(a, c->d, out_dtype == TVQ_F32, l.fast, grid, stream);
     if (rc == -1) return TVQ_ERR_UNSUPPORTED;
     if (rc != 0) return TVQ_ERR_HIP;
@@ -799,30 +826,6 @@ tvq_status tvq_decode_paged(const tvq_codec* c, const void* pool, const tvq_layo
   a.n_slots = pool_layout->batch * c->H * pool_layout->capacity_tokens;
   a.cap = (uint32_t)pool_layout->capacity_tokens;
   a.t_begin = (uint32_t)t_begin;
-  // As tvq_decode: a large range from a tile boundary whose token count is not a multiple of
-  // the tile's vectors is decoded as its whole tiles per row (one block lookup per tile), then
-  // the remaining tokens of every row.
-  const int64_t vpw = tvq::kWave / (c->d / tvq::kElemsPerLane);
-  const int64_t whole = out->tokens / vpw * vpw;
-  if (t_begin % vpw == 0 && whole > 0 && whole != out->tokens &&
-      out->batch * c->H * whole >= kSplitVectors) {
-    tvq_tensor_desc head = *out, tail = *out;
-    head.tokens = whole;
-    tail.tokens = out->tokens - whole;
-    const tvq::DecodeArgs b0 = a;
-    tvq_status st = decode_launch(c, a, &head, out_dtype, k_out, v_out, stream);
-    if (st != TVQ_OK) return st;
-    tvq::DecodeArgs b;
-    std::memset(&b, 0, sizeof(b));
-    b.cache = b0.cache;
-    b.n_slots = b0.n_slots;
-    b.cap = b0.cap;
-    b.pg = b0.pg;
-    b.t_begin = (uint32_t)(t_begin + whole);
-    const int64_t skip = whole * out->stride_t * eb;   // bytes of the head's tokens in a row
-    return decode_launch(c, b, &tail, out_dtype, (char*)k_out + skip, (char*)v_out + skip,
-                         stream);
-  }
   return decode_launch(c, a, out, out_dtype, k_out, v_out, stream);
 }
 

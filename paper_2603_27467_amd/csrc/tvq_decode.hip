@@ -77,25 +77,39 @@ __device__ __forceinline__ TilePos tile_pos(const DecodeArgs& a, uint32_t j0, in
   return p;
 }
 
-// Whole-tile rows (the call's token count a multiple of the tile's vector count): a tile's
-// vectors are consecutive tokens of one (batch, head), so the position of its first vector is
-// wave-uniform -- computed once per tile in scalar registers -- and a lane's vector is that
-// position plus its vector slot.  PAGED: t_begin is a multiple of the tile's vector count too,
-// so the tile lies in one pool block (blocks hold a power of two of at least 32 tokens); without
-// a block the tile reads records 0 .. VPW - 1 of the pool (in bounds) and is stored as zeros.
-template <bool PAGED = false>
-__device__ __forceinline__ TilePos tile_pos_rows(const DecodeArgs& a, uint32_t j0) {
-  TilePos p;
-  p.bh = fast_div(j0, a.div_t);
-  p.t = j0 - p.bh * a.div_t.div;
-  p.b = fast_div(p.bh, a.div_h);
-  p.h = p.bh - p.b * a.H;
-  p.valid = true;
+// Row tiles (see row_tiles): tile `tile` of the segment, its position wave-uniform, so that it is
+// computed once per tile in scalar registers and a lane's vector is that position plus its
+// vector slot.
+// PAGED: tiles start on multiples of the tile's vectors, so each lies in one pool block (blocks
+// hold a power of two of at least 32 tokens); vectors [lo, hi) of the tile are in the range.
+// Without a block the tile reads records 0 .. VPW - 1 of the pool (in bounds) and is stored as
+// zeros.  `t` is the token of vector lo.
+struct RowTile {
+  uint32_t b, h, t;
+  uint32_t slot;             // of vector 0
+  uint32_t lo, hi;
+  bool present;
+};
+
+template <int VPW, bool PAGED>
+__device__ __forceinline__ RowTile row_tile(const DecodeArgs& a, uint32_t tile) {
+  RowTile p;
+  const uint32_t bh = fast_div(tile, a.div_r);
+  const uint32_t first = (tile - bh * a.div_r.div) * VPW;
+  p.b = fast_div(bh, a.div_h);
+  p.h = bh - p.b * a.H;
+  p.present = true;
   if constexpr (PAGED) {
-    p.slot = paged_slot(a.pg, p.b, p.h, a.H, a.t_begin + p.t, p.present);
+    const uint32_t pos = a.pos0 + first;
+    p.lo = pos < a.t_begin ? a.t_begin - pos : 0u;
+    p.hi = min((uint32_t)VPW, a.t_begin + a.div_t.div - pos);
+    p.t = pos + p.lo - a.t_begin;
+    p.slot = paged_slot(a.pg, p.b, p.h, a.H, pos, p.present);
   } else {
-    p.slot = p.bh * a.cap + a.t_begin + p.t;
-    p.present = true;
+    p.lo = 0;
+    p.hi = VPW;
+    p.t = first;
+    p.slot = bh * a.cap + a.t_begin + p.t;
   }
   return p;
 }
@@ -112,8 +126,8 @@ struct WaveState {
   float2* lut_s;             // this wave's LDS copy, or null when it does not fit
   uint32_t sm[16];           // output sign masks, with this lane's butterfly sign folded in
   uint32_t tile0 = 0;        // the wave's first tile
-  uint32_t pslot = 0;        // paged whole-tile rows: lane x holds the pool record of the first
-                             // vector of tile tile0 + x, bit 31 set when it has no block
+  uint32_t pslot = 0;        // paged row tiles: lane x holds the pool record of the first vector
+                             // of tile tile0 + x, bit 31 set when it has no block
 };
 
 // Segment set-up common to both kernels: the wave's segment and tiles, its cos/sin table into
@@ -123,7 +137,6 @@ template <int D>
 __device__ __forceinline__ bool wave_setup(const DecodeArgs& a, WaveState<D>& w, float2* lut_rows,
                                            int lut_cap, uint32_t& tile0, uint32_t& ntiles) {
   constexpr int LPV = WaveState<D>::LPV;
-  constexpr int VPW = WaveState<D>::VPW;
   w.lane = threadIdx.x & (kWave - 1);
   w.sub = w.lane % LPV;
   w.vslot = w.lane / LPV;
@@ -132,10 +145,9 @@ __device__ __forceinline__ bool wave_setup(const DecodeArgs& a, WaveState<D>& w,
   const uint32_t li = wave / a.waves_per_seg;
   if (li >= a.num_segs) return false;
   const uint32_t wseg = wave - li * a.waves_per_seg;
-  const uint32_t tiles_in_seg = (a.nvec + VPW - 1) / VPW;
   tile0 = wseg * a.tiles_per_wave;
-  if (tile0 >= tiles_in_seg) return false;
-  ntiles = min(a.tiles_per_wave, tiles_in_seg - tile0);
+  if (tile0 >= a.seg_tiles) return false;
+  ntiles = min(a.tiles_per_wave, a.seg_tiles - tile0);
   w.sp = a.segs[a.seg_list[li]];
   for (int p = 0; p < 3; ++p) w.plane[p] = a.cache + a.n_slots * w.sp.pre[p];
   w.lut_g = (const float2*)a.lut + w.sp.lut_off;
@@ -178,7 +190,7 @@ __device__ __forceinline__ const float* build_log_levels(const WaveState<D>& w, 
 // lanes of a vector would otherwise compute the same one): lane (v, s) holds the ratio of
 // vector v in tile g + s of the group starting at tile g, from headers loaded a group ahead,
 // and tile g + x reads it from lane LPV v + x.
-// Paged whole-tile rows take the records from the wave's per-tile lookups (WaveState::pslot).
+// Paged row tiles take the records from the wave's per-tile lookups (WaveState::pslot).
 template <int D, bool PAGED = false, bool ROWS = false>
 struct LadderGroups {
   double rho = 1.0;
@@ -188,7 +200,11 @@ struct LadderGroups {
     const uint32_t tl = min(tile + (uint32_t)w.sub, last);
     uint32_t slot;
     if constexpr (PAGED && ROWS) {
-      slot = ((uint32_t)__shfl((int)w.pslot, (int)(tl - w.tile0)) & 0x7FFFFFFFu) + w.vslot;
+      const uint32_t pos = a.pos0 + (tl - fast_div(tl, a.div_r) * a.div_r.div) * WaveState<D>::VPW;
+      const uint32_t v = min(max(pos + w.vslot, a.t_begin), a.t_begin + a.div_t.div - 1) - pos;
+      slot = ((uint32_t)__shfl((int)w.pslot, (int)(tl - w.tile0)) & 0x7FFFFFFFu) + v;
+    } else if constexpr (ROWS) {
+      slot = row_tile<WaveState<D>::VPW, false>(a, tl).slot + w.vslot;
     } else {
       slot = tile_pos<PAGED>(a, tl * WaveState<D>::VPW, w.vslot).slot;
     }
@@ -248,7 +264,8 @@ __device__ __forceinline__ void reconstruct(const DecodeArgs& a, const WaveState
   }
 }
 
-__device__ __forceinline__ uint64_t out_elem(const DecodeArgs& a, uint32_t layer, const TilePos& p) {
+template <class Pos>
+__device__ __forceinline__ uint64_t out_elem(const DecodeArgs& a, uint32_t layer, const Pos& p) {
   return (uint64_t)layer * a.stride_l + (uint64_t)p.b * a.stride_b + (uint64_t)p.h * a.stride_h +
          (uint64_t)p.t * a.stride_t;
 }
@@ -274,11 +291,12 @@ __device__ __forceinline__ void store_direct(const DecodeArgs& a, const WaveStat
 // codes can leave this tile's stores in flight.  A lane past the end (its position is that of
 // the tile's first vector) stores the first vector's block again: the same bytes to the same
 // address.
-// ROWS: `pos` is the tile's first vector (tile_pos_rows), every lane's vector is in range, and
-// the host has checked that (VPW - 1) * stride_t elements fit a 32-bit byte offset.
-template <int D, bool F32OUT, bool ROWS = false>
+// ROWS: `pos` is a row tile, of which vectors [lo, hi) are in the range (PAGED; a lane outside
+// stores the nearest one's blocks again), and the host has checked that (VPW - 1) * stride_t
+// elements fit a 32-bit byte offset.
+template <int D, bool F32OUT, bool ROWS = false, bool PAGED = false, class Pos = TilePos>
 __device__ __forceinline__ void store_staged(const DecodeArgs& a, const WaveState<D>& w,
-                                             const TilePos& pos,
+                                             const Pos& pos,
                                              const uint32_t (&o)[OutWords<F32OUT>::NW],
                                              uint32_t* stg) {
   constexpr int LPV = WaveState<D>::LPV;
@@ -300,9 +318,13 @@ __device__ __forceinline__ void store_staged(const DecodeArgs& a, const WaveStat
   if constexpr (ROWS) {
     contig = a.stride_t == (uint32_t)D;
     vs = w.vslot;
+    if constexpr (PAGED) {
+      contig = contig && pos.hi - pos.lo == (uint32_t)VPW;
+      vs = min(max(vs, (int)pos.lo), (int)pos.hi - 1);
+    }
     uint8_t* const vec0 = out + out_elem(a, w.sp.layer, pos) * EB;      // wave-uniform
     dst0 = contig ? vec0 + w.lane * 16
-                  : vec0 + ((uint32_t)w.vslot * a.stride_t * (uint32_t)EB + w.sub * 16);
+                  : vec0 + ((uint32_t)(vs - (int)pos.lo) * a.stride_t * (uint32_t)EB + w.sub * 16);
   } else {
     const bool lane_ok = pos.valid && pos.t >= (uint32_t)w.vslot &&
                          pos.t - w.vslot + VPW <= a.div_t.div;
@@ -325,20 +347,18 @@ __device__ __forceinline__ void store_staged(const DecodeArgs& a, const WaveStat
   }
 }
 
-// Whole-tile rows: the position of the tile's first vector; a paged one takes its pool record
-// from the lane of the tile (looked up once per wave).
+// Row tile `tile`; a paged one takes its pool record from the lane of the tile (looked up once
+// per wave).
 template <int D, bool PAGED>
-__device__ __forceinline__ TilePos rows_pos(const DecodeArgs& a, const WaveState<D>& w,
+__device__ __forceinline__ RowTile rows_pos(const DecodeArgs& a, const WaveState<D>& w,
                                             uint32_t tile) {
+  RowTile p = row_tile<WaveState<D>::VPW, PAGED>(a, tile);
   if constexpr (PAGED) {
-    TilePos p = tile_pos_rows<false>(a, tile * WaveState<D>::VPW);
     const uint32_t r = __builtin_amdgcn_readlane(w.pslot, tile - w.tile0);
     p.present = (r >> 31) == 0u;
     p.slot = r & 0x7FFFFFFFu;
-    return p;
-  } else {
-    return tile_pos_rows<false>(a, tile * WaveState<D>::VPW);
   }
+  return p;
 }
 
 // PAGED: a position without a pool block reads record 0 of the pool (in bounds); its output is
@@ -347,8 +367,10 @@ template <int D, int WA, int NB, bool ROWS = false, bool PAGED = false>
 __device__ __forceinline__ TileCodes<WA, NB> load_tile_codes(const DecodeArgs& a,
                                                               const WaveState<D>& w, uint32_t tile) {
   if constexpr (ROWS) {
-    const TilePos p0 = rows_pos<D, PAGED>(a, w, tile);
-    return load_codes_from<WA, NB>(w.plane, w.sp.rec, p0.slot, (uint32_t)w.vslot, w.sub);
+    const RowTile p0 = rows_pos<D, PAGED>(a, w, tile);
+    uint32_t v = (uint32_t)w.vslot;
+    if constexpr (PAGED) v = min(max(v, p0.lo), p0.hi - 1);
+    return load_codes_from<WA, NB>(w.plane, w.sp.rec, p0.slot, v, w.sub);
   }
   const TilePos p = tile_pos<PAGED>(a, tile * WaveState<D>::VPW, w.vslot);
   return load_codes_at<WA, NB>(w.plane, w.sp.rec, p.slot, w.sub);
@@ -378,15 +400,17 @@ __device__ __forceinline__ void decode_tile(const DecodeArgs& a, const WaveState
   }
   uint32_t o[OutWords<F32OUT>::NW];
   reconstruct<D, F32OUT, true>(a, w, kc, r, o);
-  const TilePos p = ROWS ? rows_pos<D, PAGED>(a, w, tile)
-                        : tile_pos<PAGED>(a, tile * WaveState<D>::VPW, w.vslot);
+  const auto p = [&] {
+    if constexpr (ROWS) return rows_pos<D, PAGED>(a, w, tile);
+    else return tile_pos<PAGED>(a, tile * WaveState<D>::VPW, w.vslot);
+  }();
   if constexpr (PAGED) {
     if (!p.present) {
 #pragma unroll
       for (int i = 0; i < OutWords<F32OUT>::NW; ++i) o[i] = 0u;
     }
   }
-  store_staged<D, F32OUT, ROWS>(a, w, p, o, stg);
+  store_staged<D, F32OUT, ROWS, PAGED>(a, w, p, o, stg);
 }
 
 // Tiles tile0 .. tile0 + ntiles - 1.  MULTI: two per iteration from two code buffers, each
@@ -441,7 +465,7 @@ __global__ __launch_bounds__(kBlockThreads) void decode_fast_kernel(DecodeArgs a
   if constexpr (ROWS && PAGED) {
     // lane x: the pool record of tile tile0 + x (at most 64 tiles a wave)
     const uint32_t x = min((uint32_t)w.lane, ntiles - 1);
-    const TilePos q = tile_pos_rows<true>(a, (tile0 + x) * WaveState<D>::VPW);
+    const RowTile q = row_tile<WaveState<D>::VPW, true>(a, tile0 + x);
     w.pslot = q.present ? q.slot : 0x80000000u;
   }
   // every codebook of this kernel (n <= 256) is in LDS
@@ -558,12 +582,7 @@ int tvq_launch_decode(const tvq::DecodeArgs& a, int d, int out_f32, bool fast, u
   hipStream_t s = (hipStream_t)stream;
   const bool paged = a.pg.table != nullptr;
   const bool multi = a.tiles_per_wave > 1;
-  // whole-tile rows: every tile's vectors consecutive tokens of one (batch, head) (of one pool
-  // block when paged), and a lane's output offset within its tile, (VPW - 1) * stride_t
-  // elements, inside 32 bits
-  const uint32_t vpw = d == 128 ? 16u : 32u;
-  const bool rows = a.div_t.div % vpw == 0 && (!paged || a.t_begin % vpw == 0) &&
-                    (uint64_t)a.stride_t * vpw * (out_f32 ? 4u : 2u) < (1ull << 31);
+  const bool rows = a.rows != 0;
   if (d == 128) {
     if (out_f32) tvq::launch_decode<128, true>(a, fast, paged, multi, rows, grid, s);
     else tvq::launch_decode<128, false>(a, fast, paged, multi, rows, grid, s);

@@ -267,7 +267,7 @@ struct EncWave {
   SegParams sp;
   const void* src;
   int64_t layer_off;          // element offset of the layer and of the lane's 32 elements
-  uint32_t lane_in_bytes;     // aligned tiles: byte offset of the lane's input from the
+  uint32_t lane_in_bytes;     // whole row tiles: byte offset of the lane's input from the
                               // tile's first vector
   uint8_t* plane[3];
   const uint32_t* sm;         // the lane's 16 sign-mask words, in this wave's LDS
@@ -278,8 +278,8 @@ struct EncWave {
                               // less 8 kRoundShiftBits, modulo 2^32 (fast formats)
   uint32_t bins_off;          // n/2 on lanes holding -z (the half turn), else 0
   bool negated;               // the lane holds -z after the butterfly
-  uint32_t tile0;             // aligned paged tiles: the wave's first tile
-  uint32_t prec[2];           // aligned paged tiles: pool records (paged_records)
+  uint32_t tile0;             // paged row tiles: the wave's first tile
+  uint32_t prec[2];           // paged row tiles: pool records (paged_records)
   float shift;                // rounding shift with the half-turn of a negated lane removed
   uint32_t unneg;             // sign flip that undoes the negation (odd n)
 };
@@ -305,10 +305,9 @@ __device__ __forceinline__ bool enc_wave_setup(const EncodeArgs& a, EncWave<D>& 
   const uint32_t li = wave / a.waves_per_seg;
   if (li >= a.num_segs) return false;
   const uint32_t wseg = wave - li * a.waves_per_seg;
-  const uint32_t tiles_in_seg = (a.nvec + VPW - 1) / VPW;
   tile0 = wseg * a.tiles_per_wave;
-  if (tile0 >= tiles_in_seg) return false;
-  ntiles = min(a.tiles_per_wave, tiles_in_seg - tile0);
+  if (tile0 >= a.seg_tiles) return false;
+  ntiles = min(a.tiles_per_wave, a.seg_tiles - tile0);
   w.sp = a.segs[a.seg_list[li]];
   w.src = w.sp.kind ? a.v : a.k;
   w.layer_off = (int64_t)w.sp.layer * a.stride_l + w.sub * kElemsPerLane;
@@ -357,26 +356,34 @@ struct TileIn {
 };
 
 // PAGED: token t of sequence b goes to position seq[b] + t through the block table.
-// ALIGNED (bf16, T a multiple of the tile's vector count): the tile's vectors are consecutive
-// tokens of one (batch, head), so its position is wave-uniform (scalar arithmetic) and each
-// lane adds a fixed offset to its input address; `slot` is then the slot of the tile's first
-// vector in a contiguous cache, or the lane's own pool record (a tile may straddle two blocks
-// when seq[b] is not a multiple of its vector count).
-template <int D, bool F32IN, bool PAGED, bool ALIGNED = false>
+// Tiles (see row_tiles): kPacked; kRows, whole row tiles (T a multiple of the tile's vectors);
+// kRagged (paged), row tiles whose last one may be short: a lane past the row's end works on the
+// row's last vector and stores the same bytes as that vector's own lane.  A row tile's position is
+// wave-uniform (scalar arithmetic) and each lane adds an offset to its input address; `slot` is
+// then the slot of the tile's first vector in a contiguous cache, or the lane's own pool record
+// (a tile may straddle two blocks when seq[b] is not a multiple of its vector count).
+enum Tiles { kPacked, kRows, kRagged };
+
+template <int D, bool F32IN, bool PAGED, Tiles TL = kPacked>
 __device__ __forceinline__ TileIn<F32IN> load_tile(const EncodeArgs& a, const EncWave<D>& w,
                                                    uint32_t tile) {
   const uint32_t j0 = tile * EncWave<D>::VPW;
-  if constexpr (ALIGNED) {
-    static_assert(!F32IN, "aligned tiles: bf16 input");
-    const uint32_t bh = fast_div(j0, a.div_t);
-    const uint32_t t = j0 - bh * a.div_t.div;
+  if constexpr (TL != kPacked) {
+    static_assert(!F32IN, "row tiles: bf16 input");
+    const uint32_t bh = fast_div(tile, a.div_r);
+    const uint32_t t = (tile - bh * a.div_r.div) * EncWave<D>::VPW;
     const uint32_t b = fast_div(bh, a.div_h);
     const uint32_t h = bh - b * a.H;
     const uint16_t* base = (const uint16_t*)w.src + (int64_t)w.sp.layer * a.stride_l +
                            (uint64_t)b * a.stride_b + (uint64_t)h * a.stride_h +
                            (uint64_t)t * a.stride_t;
     TileIn<F32IN> in;
-    load_words<16>((const uint32_t*)((const uint8_t*)base + w.lane_in_bytes), in.raw.w);
+    uint32_t off = w.lane_in_bytes;
+    if constexpr (TL == kRagged) {
+      const uint32_t v = min((uint32_t)w.vslot, a.div_t.div - 1 - t);
+      off = ((uint32_t)w.sub * kElemsPerLane + v * a.stride_t) * 2u;
+    }
+    load_words<16>((const uint32_t*)((const uint8_t*)base + off), in.raw.w);
     if constexpr (PAGED) {
       // looked up at the wave's start (paged_records)
       const uint32_t c = (tile - w.tile0) * EncWave<D>::VPW + (uint32_t)w.vslot;
@@ -414,11 +421,11 @@ __device__ __forceinline__ TileIn<F32IN> load_tile(const EncodeArgs& a, const En
   return in;
 }
 
-// Aligned paged tiles: the pool record of every vector of the wave's tiles, looked up before
+// Paged row tiles: the pool record of every vector of the wave's tiles, looked up before
 // the tile loop so that the table reads do not wait inside it.  Vector c = x VPW + v (vector
 // slot v of tile tile0 + x) is held in register c / 64 of lane c % 64, bit 31 set when it has
 // no block, and load_tile reads it back with a lane permute (an array indexed by the tile would
-// be placed in scratch memory).  Every tile of an aligned launch is whole.
+// be placed in scratch memory).  Vectors past a row's end take its last one's record.
 template <int D>
 __device__ __forceinline__ void paged_records(const EncodeArgs& a, EncWave<D>& w, uint32_t tile0,
                                               uint32_t ntiles) {
@@ -430,9 +437,9 @@ __device__ __forceinline__ void paged_records(const EncodeArgs& a, EncWave<D>& w
     w.prec[k] = 0x80000000u;
     if (k * kWave >= VPW * kFastTilesPerWave) continue;
     const uint32_t c = k * kWave + (threadIdx.x & (kWave - 1));
-    const uint32_t j = min(tile0 + c / VPW, tile0 + ntiles - 1) * VPW + c % VPW;
-    const uint32_t bh = fast_div(j, a.div_t);
-    const uint32_t t = j - bh * a.div_t.div;
+    const uint32_t tile = min(tile0 + c / VPW, tile0 + ntiles - 1);
+    const uint32_t bh = fast_div(tile, a.div_r);
+    const uint32_t t = min((tile - bh * a.div_r.div) * VPW + c % VPW, a.div_t.div - 1);
     const uint32_t b = fast_div(bh, a.div_h);
     const uint32_t h = bh - b * a.H;
     const int32_t p0 = a.pg.seq[b];
@@ -619,16 +626,16 @@ __device__ __forceinline__ void transform_tile(const EncWave<D>& w, const Raw<F3
   }
 }
 
-// Store a lane's 16 norm codes (low bits of qc) and its vector's header.  ALIGNED: the tile's
+// Store a lane's 16 norm codes (low bits of qc) and its vector's header.  UNIFORM: the tile's
 // records are consecutive from the uniform record of its first vector (the lane's offset is
 // added as a 32-bit offset to that scalar address).
-template <int D, int NB, bool ALIGNED>
+template <int D, int NB, bool UNIFORM>
 __device__ __forceinline__ void store_norms(const EncWave<D>& w, uint32_t slot, uint32_t nbits,
                                             const uint32_t (&qc)[kPairsPerLane], float rmin,
                                             float rmax) {
   uint8_t* rec_nrm = w.plane[1] + (uint64_t)slot * w.sp.rec[1];
-  const uint32_t lane_nrm = ALIGNED ? (uint32_t)w.vslot * w.sp.rec[1] : 0u;
-  const uint32_t lane_hdr = ALIGNED ? (uint32_t)w.vslot * 8u : 0u;
+  const uint32_t lane_nrm = UNIFORM ? (uint32_t)w.vslot * w.sp.rec[1] : 0u;
+  const uint32_t lane_hdr = UNIFORM ? (uint32_t)w.vslot * 8u : 0u;
   if constexpr (NB == 4)
     store_chunk<4>(rec_nrm + (lane_nrm + 8u * (uint32_t)w.sub), pack16_nibbles(qc));
   else if constexpr (NB == 8)
@@ -649,7 +656,7 @@ __device__ __forceinline__ void store_norms(const EncWave<D>& w, uint32_t slot, 
 // after the tile loop, on the tile's input loaded again, and overwrites the codes and header
 // the loop stored: its temporaries and constants then stay out of the loop's registers.  The
 // norms are formed twice (for the extremes, then for the codes) rather than kept.
-template <int D, bool F32IN, int NB, bool PAGED, bool MF, bool ALIGNED>
+template <int D, bool F32IN, int NB, bool PAGED, bool MF, bool UNIFORM>
 __device__ __forceinline__ void encode_norms_f64(const EncWave<D>& w, const TileIn<F32IN>& in) {
   constexpr int LPV = EncWave<D>::LPV;
   const uint32_t nbits = NB ? (uint32_t)NB : w.sp.bits;
@@ -684,11 +691,11 @@ __device__ __forceinline__ void encode_norms_f64(const EncWave<D>& w, const Tile
       qc[i] = code_of_t(ln_f64_lean(r * rc) * scale, lv);
     }
   }
-  if (!PAGED || in.ok) store_norms<D, NB, ALIGNED>(w, in.slot, nbits, qc, rmin, rmax);
+  if (!PAGED || in.ok) store_norms<D, NB, UNIFORM>(w, in.slot, nbits, qc, rmin, rmax);
 }
 
 template <int D, bool F32IN, int WA, int NB, bool PAGED, bool MF = false, bool BINS = false,
-          bool ALIGNED = false>
+          bool UNIFORM = false>
 __device__ __forceinline__ bool encode_tile(const EncodeArgs& a, const EncWave<D>& w,
                                             const TileIn<F32IN>& in) {
   static_assert(!MF || (D == 128 && !F32IN), "matrix-core front end: d = 128, bf16 input");
@@ -733,7 +740,7 @@ __device__ __forceinline__ bool encode_tile(const EncodeArgs& a, const EncWave<D
   const bool f64_norms = (kFixed || mode != 0) && !fast_norm;   // the caller's fp64 norm pass
 
   // ---- norms (first: the squared norms are then dead before the angle codes exist) ----
-  static_assert(!ALIGNED || (kFixed && !MF && !PAGED), "aligned tiles: fast formats");
+  static_assert(!UNIFORM || (kFixed && !MF && !PAGED), "row tiles: fast formats");
   if (!kFixed && mode == 0) {
     // fp32 norms, rounded once from the fp64 value
     uint8_t* rec_nrm = w.plane[1] + (uint64_t)in.slot * sp.rec[1];
@@ -774,7 +781,7 @@ __device__ __forceinline__ bool encode_tile(const EncodeArgs& a, const EncWave<D
         qc[i] = __float_as_uint(
             __builtin_fmaf(__builtin_amdgcn_logf(s2[i] * rs) - k0, scale, kRoundShift));
     }
-    if (store) store_norms<D, kFixed ? NB : 0, ALIGNED>(w, in.slot, nbits, qc, rmin, rmax);
+    if (store) store_norms<D, kFixed ? NB : 0, UNIFORM>(w, in.slot, nbits, qc, rmin, rmax);
   }
 
   // ---- angle codes ----
@@ -819,7 +826,7 @@ __device__ __forceinline__ bool encode_tile(const EncodeArgs& a, const EncWave<D
   }
   if (store) {
     if constexpr (kFixed) {
-      const uint32_t lane_ang = ALIGNED ? (uint32_t)w.vslot * sp.rec[0] : 0u;
+      const uint32_t lane_ang = UNIFORM ? (uint32_t)w.vslot * sp.rec[0] : 0u;
       store_lane_chunk<WA>(rec_ang, lane_ang, w.sub, pack16<WA>(kc));
     } else {
       store_codes_any(rec_ang, w.sub, sp.w, kc);
@@ -836,13 +843,13 @@ __device__ __forceinline__ bool encode_tile(const EncodeArgs& a, const EncWave<D
 // the same kernel would raise its register count); it evaluates the angles (angle_bits)
 // rather than staging the bin table for a single tile, which made those short launches ~30%
 // slower.  Both give the exact code outside the flag zone.
-template <int D, bool MULTI, int WA, int NB, bool PAGED, bool MF = false, bool ALIGNED = false>
+template <int D, bool MULTI, int WA, int NB, bool PAGED, bool MF = false, Tiles TL = kPacked>
 __device__ void encode_tiles_fast(const EncodeArgs& a, const EncWave<D>& w, uint32_t tile0,
                                   uint32_t ntiles) {
   const uint32_t last = tile0 + ntiles - 1;
-  // aligned pool records are per lane (load_tile): the stores then take the lane's own slot
-  constexpr bool SA = ALIGNED && !PAGED;
-  TileIn<false> ia = load_tile<D, false, PAGED, ALIGNED>(a, w, tile0);
+  // pool records are per lane (load_tile): the stores then take the lane's own slot
+  constexpr bool SA = TL != kPacked && !PAGED;
+  TileIn<false> ia = load_tile<D, false, PAGED, TL>(a, w, tile0);
   stage_tables<D>(a, w);
   if constexpr (!MULTI) {
     if (encode_tile<D, false, WA, NB, PAGED, MF, false, SA>(a, w, ia))
@@ -852,16 +859,16 @@ __device__ void encode_tiles_fast(const EncodeArgs& a, const EncWave<D>& w, uint
   uint32_t redo = 0;    // tiles (bit tile - tile0) whose norms take the fp64 pass
   for (uint32_t t = tile0; t <= last; t += 2) {
     const uint32_t t1 = min(t + 1, last);
-    const TileIn<false> ib = load_tile<D, false, PAGED, ALIGNED>(a, w, t1);
+    const TileIn<false> ib = load_tile<D, false, PAGED, TL>(a, w, t1);
     if (encode_tile<D, false, WA, NB, PAGED, MF, true, SA>(a, w, ia)) redo |= 1u << (t - tile0);
-    ia = load_tile<D, false, PAGED, ALIGNED>(a, w, min(t + 2, last));
+    ia = load_tile<D, false, PAGED, TL>(a, w, min(t + 2, last));
     if (encode_tile<D, false, WA, NB, PAGED, MF, true, SA>(a, w, ib)) redo |= 1u << (t1 - tile0);
   }
   while (redo != 0) {
     const uint32_t k = __builtin_ctz(redo);
     redo &= redo - 1;
     encode_norms_f64<D, false, NB, PAGED, MF, SA>(
-        w, load_tile<D, false, PAGED, ALIGNED>(a, w, tile0 + k));
+        w, load_tile<D, false, PAGED, TL>(a, w, tile0 + k));
   }
 }
 
@@ -883,35 +890,35 @@ __global__ __launch_bounds__(kBlockThreads) void encode_mfma_kernel(EncodeArgs a
   }
 }
 
-// ALIGNED: see load_tile (multi-tile launches only).  N128: the segment list holds n = 128
+// TL: see load_tile (row tiles: multi-tile launches only).  N128: the segment list holds n = 128
 // segments; launches without them use the instantiation without that format's two tile loops,
 // whose presence costs the others 2% (the 32-layer n = 64 prefill of 4096 tokens at d = 128:
 // 156.0 us without, 159.5 us with).
-template <int D, bool MULTI, bool PAGED, bool ALIGNED = false, bool N128 = false>
+template <int D, bool MULTI, bool PAGED, Tiles TL = kPacked, bool N128 = false>
 __global__ __launch_bounds__(kBlockThreads) void encode_fast_kernel(EncodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t s_sm[kWavesPerBlock][D / 2];
   __shared__ u32x2 s_bins[kWavesPerBlock][kBinRows];
   EncWave<D> w;
   uint32_t tile0, ntiles;
   if (!enc_wave_setup<D>(a, w, s_sm, tile0, ntiles, MULTI ? s_bins : nullptr)) return;
-  static_assert(!(PAGED && ALIGNED) || MULTI, "aligned tiles: multi-tile launches");
-  if constexpr (PAGED && ALIGNED) paged_records<D>(a, w, tile0, ntiles);
+  static_assert(TL == kPacked || MULTI, "row tiles: multi-tile launches");
+  if constexpr (PAGED && TL != kPacked) paged_records<D>(a, w, tile0, ntiles);
   if constexpr (N128) {
     if (w.sp.w == 7) {
       if (w.sp.mode == 1)
-        encode_tiles_fast<D, MULTI, 7, 8, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
+        encode_tiles_fast<D, MULTI, 7, 8, PAGED, false, TL>(a, w, tile0, ntiles);
       else
-        encode_tiles_fast<D, MULTI, 7, 4, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
+        encode_tiles_fast<D, MULTI, 7, 4, PAGED, false, TL>(a, w, tile0, ntiles);
       return;
     }
   }
   const bool wide = w.sp.w == 8;
   if (w.sp.mode == 1) {
-    if (wide) encode_tiles_fast<D, MULTI, 8, 8, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
-    else encode_tiles_fast<D, MULTI, 6, 8, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
+    if (wide) encode_tiles_fast<D, MULTI, 8, 8, PAGED, false, TL>(a, w, tile0, ntiles);
+    else encode_tiles_fast<D, MULTI, 6, 8, PAGED, false, TL>(a, w, tile0, ntiles);
   } else {
-    if (wide) encode_tiles_fast<D, MULTI, 8, 4, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
-    else encode_tiles_fast<D, MULTI, 6, 4, PAGED, false, ALIGNED>(a, w, tile0, ntiles);
+    if (wide) encode_tiles_fast<D, MULTI, 8, 4, PAGED, false, TL>(a, w, tile0, ntiles);
+    else encode_tiles_fast<D, MULTI, 6, 4, PAGED, false, TL>(a, w, tile0, ntiles);
   }
 }
 
@@ -931,35 +938,38 @@ __global__ __launch_bounds__(kBlockThreads) void encode_generic_kernel(EncodeArg
 }
 
 template <int D, bool PAGED, bool N128>
-void launch_fast(const EncodeArgs& a, bool multi, bool aligned, unsigned grid, hipStream_t s) {
+void launch_fast(const EncodeArgs& a, unsigned grid, hipStream_t s) {
   const dim3 g(grid), block(kBlockThreads);
-  if (multi && aligned)
-    hipLaunchKernelGGL((encode_fast_kernel<D, true, PAGED, true, N128>), g, block, 0, s, a);
-  else if (multi)
-    hipLaunchKernelGGL((encode_fast_kernel<D, true, PAGED, false, N128>), g, block, 0, s, a);
+  if constexpr (PAGED) {
+    // where the last tile of a row is short the lanes' input offsets are formed per tile
+    if (a.rows != 0 && a.div_t.div % EncWave<D>::VPW != 0) {
+      hipLaunchKernelGGL((encode_fast_kernel<D, true, true, kRagged, N128>), g, block, 0, s, a);
+      return;
+    }
+  }
+  if (a.rows != 0)
+    hipLaunchKernelGGL((encode_fast_kernel<D, true, PAGED, kRows, N128>), g, block, 0, s, a);
+  else if (a.tiles_per_wave > 1)
+    hipLaunchKernelGGL((encode_fast_kernel<D, true, PAGED, kPacked, N128>), g, block, 0, s, a);
   else
-    hipLaunchKernelGGL((encode_fast_kernel<D, false, PAGED, false, N128>), g, block, 0, s, a);
+    hipLaunchKernelGGL((encode_fast_kernel<D, false, PAGED, kPacked, N128>), g, block, 0, s, a);
 }
 
 template <int D, bool PAGED>
 void launch_encode(const EncodeArgs& a, int in_f32, bool fast, unsigned grid, hipStream_t s) {
   const dim3 block(kBlockThreads);
-  const bool multi = a.tiles_per_wave > 1;
   if constexpr (D == 128 && !PAGED) {
     if (fast && a.mfma_front) {
+      const bool multi = a.tiles_per_wave > 1;
       if (multi) hipLaunchKernelGGL((encode_mfma_kernel<true>), dim3(grid), block, 0, s, a);
       else hipLaunchKernelGGL((encode_mfma_kernel<false>), dim3(grid), block, 0, s, a);
       return;
     }
   }
-  // aligned tiles: whole tiles per (batch, head), and every lane's input offset from its
-  // tile's first vector, (VPW - 1) * stride_t + d elements of bf16, inside 32 bits
-  constexpr uint32_t VPW = EncWave<D>::VPW;
-  const bool aligned = a.div_t.div % VPW == 0 && (uint64_t)a.stride_t * VPW * 2u < (1ull << 31);
   if (fast && a.has_n128)
-    launch_fast<D, PAGED, true>(a, multi, aligned, grid, s);
+    launch_fast<D, PAGED, true>(a, grid, s);
   else if (fast)
-    launch_fast<D, PAGED, false>(a, multi, aligned, grid, s);
+    launch_fast<D, PAGED, false>(a, grid, s);
   else if (in_f32)
     hipLaunchKernelGGL((encode_generic_kernel<D, true, PAGED>), dim3(grid), block, 0, s, a);
   else

@@ -25,7 +25,7 @@ from workloads import LayerCfg, NORM_F32, NORM_LINEAR, NORM_LOG
 
 from parity import bf16_to_f64 as parity_bf16
 from parity import (DecodeCheck, Setup, attention_error_bar, bf16_bits_to_torch, bf16_differ,
-                    check_decoded, compare_decode, compare_encode, run_encode,
+                    check_decoded, compare_decode, compare_encode, gather_paged, run_encode,
                     setup_from_workload, torch_to_np, untouched_outside)
 
 pytestmark = pytest.mark.gpu
@@ -523,26 +523,33 @@ def test_multi_tile_encode_sampled(gpu, d, L, B, T, t_begin, pad):
     assert stats["hdr_ulp"] <= 2
 
 
-@pytest.mark.parametrize("d,L,B,T,t_begin", [
-    (128, 2, 2, 4112, 5),        # whole tiles per (batch, head), two tiles per wave
-    (128, 2, 2, 4101, 3),        # ragged rows
-    (64, 2, 2, 8197, 0),
-    (64, 2, 1, 33, 2),           # one tile per wave, a tile of one vector
+@pytest.mark.parametrize("d,L,B,T,t_begin,pad", [
+    (128, 2, 4, 4112, 5, 0),     # whole tiles per (batch, head) row, two tiles per wave
+    (128, 2, 4, 4101, 3, 0),     # row tiles, the last one of 5 vectors
+    (128, 2, 4, 4111, 15, 32),   # the last one lacks a vector; strided views
+    (128, 4, 56, 135, 16, 0),    # short rows, 8.4 tiles: cut into tiles of their own
+    (128, 4, 56, 129, 1, 0),     # too short for that (8.1 tiles): packed tiles
+    (64, 2, 4, 8197, 0, 0),
+    (64, 2, 4, 8223, 31, 16),
+    (64, 2, 1, 33, 2, 0),        # one tile per wave, a tile of one vector
 ])
-def test_n128_multi_tile(gpu, d, L, B, T, t_begin):
-    """n = 128 (7-bit codes: 14-byte chunks, odd lanes starting between dwords) with both norm
-    modes through the multi-tile kernels, contiguous and through a pool in shuffled blocks:
-    codes and headers of the last tiles of every segment and of 600 random vectors against the
-    oracle's encode, slots outside the range untouched, the same codes from the pool, and the
-    decoded values of those vectors (fp32 and bf16) against the oracle's decode of the bytes."""
+def test_ragged_rows_and_n128(gpu, d, L, B, T, t_begin, pad):
+    """The tiles of multi-tile launches at their edges (row tiles whose last one is short, from
+    cache positions off a tile boundary, and packed ones), with n = 128 (7-bit codes: 14-byte
+    chunks, odd lanes starting between dwords) and both norm modes, contiguous and through a
+    pool in shuffled blocks, from and into views of token stride d + pad: codes and headers of
+    the last tiles of every segment and of 600 random vectors against the oracle's encode, slots
+    outside the range untouched, and the decoded values of those vectors (fp32 and bf16) against
+    the oracle's decode of the bytes."""
     import torch
     H = 4 if T > 100 else 2
-    table = [LayerCfg(128, 128), LayerCfg(64, 128)][:L]
+    table = [LayerCfg(128, 128), LayerCfg(64, 128), LayerCfg(256, 64), LayerCfg(64, 64)][:L]
     w = workloads.get("C2")
     s = Setup(L, H, d, table, workloads.sign_table(17, L, d)).build()
     k, v = _draw(w, L, B, H, T, d, "bf16", 18)
-    kd, vd = bf16_bits_to_torch(k).cuda(), bf16_bits_to_torch(v).cuda()
-    T_cap = T + 16
+    kd, vd = (torch.zeros((L, B, H, T, d + pad), dtype=torch.bfloat16, device="cuda")[..., :d]
+              .copy_(bf16_bits_to_torch(x)) for x in (k, v))
+    T_cap = T + 32
     lay = s.gpu.layout(B, T_cap)
     cache = torch.full((lay.total_bytes,), 0xAB, dtype=torch.uint8, device="cuda")
     s.gpu.encode(kd, vd, cache, lay, t_begin=t_begin)
@@ -557,20 +564,18 @@ def test_n128_multi_tile(gpu, d, L, B, T, t_begin):
     outs, pouts = {}, {}
     for dt in (torch.float32, torch.bfloat16):
         for dst, paged in ((outs, False), (pouts, True)):
-            ko = torch.full((L, B, H, T, d), float("nan"), dtype=dt, device="cuda")
-            vo = torch.full_like(ko, float("nan"))
+            full = [torch.full((L, B, H, T, d + pad), 7.0, dtype=dt, device="cuda")
+                    for _ in range(2)]
+            ko, vo = (x[..., :d].fill_(float("nan")) for x in full)
             if paged:
                 s.gpu.decode_paged(pool, play, tab, t_begin, t_begin + T, ko, vo)
             else:
                 s.gpu.decode(cache, lay, t_begin, t_begin + T, ko, vo)
-            dst[dt] = (ko, vo)
-        torch.cuda.synchronize()
-        # the same codes, however they are stored, decode to the same bits
-        for kind in range(2):
-            assert torch.equal(outs[dt][kind].view(torch.uint8), pouts[dt][kind].view(torch.uint8))
-        outs[dt] = tuple(torch_to_np(x) for x in outs[dt])
+            assert all((x[..., d:] == 7.0).all() for x in full)     # nothing between the vectors
+            dst[dt] = (torch_to_np(ko.contiguous()), torch_to_np(vo.contiguous()))
     host = torch_to_np(cache)
     assert untouched_outside(host, s, B, T, T_cap, t_begin, 0xAB)
+    gath = [gather_paged(torch_to_np(pool), s, B * per, bt, order[b], 0) for b in range(B)]
     nvec = B * H * T
     vpw = 64 // (d // 32)
     rng = np.random.default_rng(4)
@@ -585,18 +590,22 @@ def test_n128_multi_tile(gpu, d, L, B, T, t_begin):
         x = ((k if kind == 0 else v)[l, b, h, t].astype(np.uint32) << 16).view(np.float32)
         kd_ = s.orc.kinds[2 * l + kind]
         ref = oracle.encode_vector(x, s.signs[l], kd_)
-        kg, qg, rn, hg = s.orc.read_vector(host, B, T_cap, l, kind, b, h, t_begin + t)
-        unflagged += int(((kg != ref.k) & ~oracle.angle_flags(ref.u, kd_.n)).sum())
-        unflagged += int(((qg != ref.q) & ~oracle.norm_flags(ref.t, kd_.norm_bits, ref.hdr,
-                                                              kd_.norm_mode)).sum())
-        du = np.abs(hg.view(np.int32).astype(np.int64) - ref.hdr.view(np.int32).astype(np.int64))
-        hdr_ulp = max(hdr_ulp, int(du.max()))
-        dec = oracle.decode_vector(kd_, s.signs[l], kg, qg, rn, hg, "f64")
-        mirror = oracle.decode_vector(kd_, s.signs[l], kg, qg, rn, hg, "f32")
-        check_decoded(chk32, dec[None], d, g32=outs[torch.float32][kind][l, b, h, t][None],
-                      mirror32=mirror[None])
-        check_decoded(chk16, dec[None], d, g16=outs[torch.bfloat16][kind][l, b, h, t][None])
-    _say(f"[n=128 d={d} T={T}] {len(picks)} vectors, fp32 {chk32.line()}; bf16 {chk16.line()}")
+        for got, vec in ((outs, s.orc.read_vector(host, B, T_cap, l, kind, b, h, t_begin + t)),
+                         (pouts, s.orc.read_vector(gath[b], 1, per * bt, l, kind, 0, h,
+                                                   t_begin + t))):
+            kg, qg, rn, hg = vec
+            unflagged += int(((kg != ref.k) & ~oracle.angle_flags(ref.u, kd_.n)).sum())
+            unflagged += int(((qg != ref.q) & ~oracle.norm_flags(ref.t, kd_.norm_bits, ref.hdr,
+                                                                  kd_.norm_mode)).sum())
+            du = np.abs(hg.view(np.int32).astype(np.int64) -
+                        ref.hdr.view(np.int32).astype(np.int64))
+            hdr_ulp = max(hdr_ulp, int(du.max()))
+            dec = oracle.decode_vector(kd_, s.signs[l], kg, qg, rn, hg, "f64")
+            mirror = oracle.decode_vector(kd_, s.signs[l], kg, qg, rn, hg, "f32")
+            check_decoded(chk32, dec[None], d, g32=got[torch.float32][kind][l, b, h, t][None],
+                          mirror32=mirror[None])
+            check_decoded(chk16, dec[None], d, g16=got[torch.bfloat16][kind][l, b, h, t][None])
+    _say(f"[ragged rows d={d} T={T}] {len(picks)} vectors, fp32 {chk32.line()}; bf16 {chk16.line()}")
     assert unflagged == 0 and hdr_ulp <= 2      # the bars of the other multi-tile encode tests
     assert chk32.ok() and chk16.ok()
 
