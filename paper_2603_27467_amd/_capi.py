@@ -168,26 +168,28 @@ def tvq_layout_for_config(cfg: tvq_config, batch: int, capacity_tokens: int) -> 
     return lay
 
 
+# The calls of a step pass addresses and floats as they are: the argument types declared above
+# convert them, at a fraction of the cost of a ctypes object per argument.
 def tvq_encode(handle: int, in_dtype: int, k_ptr: int, v_ptr: int, desc: tvq_tensor_desc,
                t_begin: int, cache_ptr: int, lay: tvq_layout, stream: int = 0) -> None:
-    _check(load_library().tvq_encode(ctypes.c_void_p(handle), in_dtype, ctypes.c_void_p(k_ptr),
-                                     ctypes.c_void_p(v_ptr), ctypes.byref(desc), t_begin,
-                                     ctypes.c_void_p(cache_ptr), ctypes.byref(lay),
-                                     ctypes.c_void_p(stream)), "tvq_encode")
+    _check(load_library().tvq_encode(handle, in_dtype, k_ptr,
+                                     v_ptr, ctypes.byref(desc), t_begin,
+                                     cache_ptr, ctypes.byref(lay),
+                                     stream), "tvq_encode")
 
 
 def tvq_decode(handle: int, cache_ptr: int, lay: tvq_layout, t_begin: int, t_end: int,
                out_dtype: int, k_ptr: int, v_ptr: int, desc: tvq_tensor_desc,
                stream: int = 0) -> None:
-    _check(load_library().tvq_decode(ctypes.c_void_p(handle), ctypes.c_void_p(cache_ptr),
+    _check(load_library().tvq_decode(handle, cache_ptr,
                                      ctypes.byref(lay), t_begin, t_end, out_dtype,
-                                     ctypes.c_void_p(k_ptr), ctypes.c_void_p(v_ptr),
-                                     ctypes.byref(desc), ctypes.c_void_p(stream)), "tvq_decode")
+                                     k_ptr, v_ptr,
+                                     ctypes.byref(desc), stream), "tvq_decode")
 
 
 def tvq_attention_workspace(handle: int, batch: int, num_q_heads: int, t_end: int) -> int:
     out = ctypes.c_int64(0)
-    _check(load_library().tvq_attention_workspace(ctypes.c_void_p(handle), batch, num_q_heads,
+    _check(load_library().tvq_attention_workspace(handle, batch, num_q_heads,
                                                   t_end, ctypes.byref(out)),
            "tvq_attention_workspace")
     return int(out.value)
@@ -197,9 +199,9 @@ def tvq_attention_decode(handle: int, cache_ptr: int, lay: tvq_layout, layer: in
                          num_q_heads: int, scale: float, q_dtype: int, q_ptr: int, o_dtype: int,
                          o_ptr: int, ws_ptr: int, ws_bytes: int, stream: int = 0) -> None:
     _check(load_library().tvq_attention_decode(
-        ctypes.c_void_p(handle), ctypes.c_void_p(cache_ptr), ctypes.byref(lay), layer, t_end,
-        num_q_heads, ctypes.c_float(scale), q_dtype, ctypes.c_void_p(q_ptr), o_dtype,
-        ctypes.c_void_p(o_ptr), ctypes.c_void_p(ws_ptr), ws_bytes, ctypes.c_void_p(stream)),
+        handle, cache_ptr, ctypes.byref(lay), layer, t_end,
+        num_q_heads, scale, q_dtype, q_ptr, o_dtype,
+        o_ptr, ws_ptr, ws_bytes, stream),
         "tvq_attention_decode")
 
 
@@ -207,26 +209,26 @@ def tvq_attention_decode_noalloc(handle: int, cache_ptr: int, lay: tvq_layout, l
                                  t_end: int, num_q_heads: int, scale: float, q_dtype: int,
                                  q_ptr: int, o_dtype: int, o_ptr: int, stream: int = 0) -> None:
     _check(load_library().tvq_attention_decode_noalloc(
-        ctypes.c_void_p(handle), ctypes.c_void_p(cache_ptr), ctypes.byref(lay), layer, t_end,
-        num_q_heads, ctypes.c_float(scale), q_dtype, ctypes.c_void_p(q_ptr), o_dtype,
-        ctypes.c_void_p(o_ptr), ctypes.c_void_p(stream)), "tvq_attention_decode_noalloc")
+        handle, cache_ptr, ctypes.byref(lay), layer, t_end,
+        num_q_heads, scale, q_dtype, q_ptr, o_dtype,
+        o_ptr, stream), "tvq_attention_decode_noalloc")
 
 
 def tvq_encode_mfma(handle: int, k_ptr: int, v_ptr: int, desc: tvq_tensor_desc, t_begin: int,
                     cache_ptr: int, lay: tvq_layout, stream: int = 0) -> None:
     _check(load_library().tvq_encode_mfma(
-        ctypes.c_void_p(handle), ctypes.c_void_p(k_ptr), ctypes.c_void_p(v_ptr),
-        ctypes.byref(desc), t_begin, ctypes.c_void_p(cache_ptr), ctypes.byref(lay),
-        ctypes.c_void_p(stream)), "tvq_encode_mfma")
+        handle, k_ptr, v_ptr,
+        ctypes.byref(desc), t_begin, cache_ptr, ctypes.byref(lay),
+        stream), "tvq_encode_mfma")
 
 
 def tvq_encode_paged(handle: int, in_dtype: int, k_ptr: int, v_ptr: int, desc: tvq_tensor_desc,
                      positions_ptr: int, table_ptr: int, max_blocks: int, pool_ptr: int,
                      pool_lay: tvq_layout, stream: int = 0) -> None:
     _check(load_library().tvq_encode_paged(
-        ctypes.c_void_p(handle), in_dtype, ctypes.c_void_p(k_ptr), ctypes.c_void_p(v_ptr),
-        ctypes.byref(desc), ctypes.c_void_p(positions_ptr), ctypes.c_void_p(table_ptr),
-        max_blocks, ctypes.c_void_p(pool_ptr), ctypes.byref(pool_lay), ctypes.c_void_p(stream)),
+        handle, in_dtype, k_ptr, v_ptr,
+        ctypes.byref(desc), positions_ptr, table_ptr,
+        max_blocks, pool_ptr, ctypes.byref(pool_lay), stream),
         "tvq_encode_paged")
 
 
@@ -234,17 +236,17 @@ def tvq_decode_paged(handle: int, pool_ptr: int, pool_lay: tvq_layout, table_ptr
                      max_blocks: int, t_begin: int, t_end: int, out_dtype: int, k_ptr: int,
                      v_ptr: int, desc: tvq_tensor_desc, stream: int = 0) -> None:
     _check(load_library().tvq_decode_paged(
-        ctypes.c_void_p(handle), ctypes.c_void_p(pool_ptr), ctypes.byref(pool_lay),
-        ctypes.c_void_p(table_ptr), max_blocks, t_begin, t_end, out_dtype,
-        ctypes.c_void_p(k_ptr), ctypes.c_void_p(v_ptr), ctypes.byref(desc),
-        ctypes.c_void_p(stream)), "tvq_decode_paged")
+        handle, pool_ptr, ctypes.byref(pool_lay),
+        table_ptr, max_blocks, t_begin, t_end, out_dtype,
+        k_ptr, v_ptr, ctypes.byref(desc),
+        stream), "tvq_decode_paged")
 
 
 def tvq_attention_paged_workspace(handle: int, batch: int, num_q_heads: int, max_ctx: int,
                                   block_tokens: int) -> int:
     out = ctypes.c_int64(0)
     _check(load_library().tvq_attention_paged_workspace(
-        ctypes.c_void_p(handle), batch, num_q_heads, max_ctx, block_tokens, ctypes.byref(out)),
+        handle, batch, num_q_heads, max_ctx, block_tokens, ctypes.byref(out)),
         "tvq_attention_paged_workspace")
     return int(out.value)
 
@@ -254,10 +256,10 @@ def tvq_attention_paged(handle: int, pool_ptr: int, pool_lay: tvq_layout, table_
                         num_q_heads: int, scale: float, q_dtype: int, q_ptr: int, o_dtype: int,
                         o_ptr: int, ws_ptr: int, ws_bytes: int, stream: int = 0) -> None:
     _check(load_library().tvq_attention_paged(
-        ctypes.c_void_p(handle), ctypes.c_void_p(pool_ptr), ctypes.byref(pool_lay),
-        ctypes.c_void_p(table_ptr), max_blocks, ctypes.c_void_p(ctx_ptr), max_ctx, batch, layer,
-        num_q_heads, ctypes.c_float(scale), q_dtype, ctypes.c_void_p(q_ptr), o_dtype,
-        ctypes.c_void_p(o_ptr), ctypes.c_void_p(ws_ptr), ws_bytes, ctypes.c_void_p(stream)),
+        handle, pool_ptr, ctypes.byref(pool_lay),
+        table_ptr, max_blocks, ctx_ptr, max_ctx, batch, layer,
+        num_q_heads, scale, q_dtype, q_ptr, o_dtype,
+        o_ptr, ws_ptr, ws_bytes, stream),
         "tvq_attention_paged")
 
 

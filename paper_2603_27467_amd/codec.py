@@ -24,7 +24,8 @@ class LayerCfg:
 def _stream_handle(stream) -> int:
     import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream's handle without a Stream object around it (2 us a call)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -162,8 +163,8 @@ class Codec:
         dts = {torch.bfloat16: C.TVQ_BF16, torch.float32: C.TVQ_F32}
         if q.dtype not in dts or out.dtype not in dts:
             raise ValueError("q/out must be bf16 or fp32")
-        need = self.attention_workspace_bytes(q.shape[0], q.shape[1], t_end)
-        if workspace is None:
+        if workspace is None:       # the call itself checks the size of a given one
+            need = self.attention_workspace_bytes(q.shape[0], q.shape[1], t_end)
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
         elif workspace.dtype != torch.uint8 or not workspace.is_cuda or \
                 not workspace.is_contiguous():
@@ -257,9 +258,9 @@ class Codec:
         B = q.shape[0]
         if block_table.dim() != 2 or block_table.shape[0] != B or ctx_lens.shape != (B,):
             raise ValueError("block_table [B, max_blocks] and ctx_lens [B] must match q")
-        need = self.attention_paged_workspace_bytes(B, q.shape[1], max_ctx,
-                                                    pool_lay.capacity_tokens)
-        if workspace is None:
+        if workspace is None:       # the call itself checks the size of a given one
+            need = self.attention_paged_workspace_bytes(B, q.shape[1], max_ctx,
+                                                        pool_lay.capacity_tokens)
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
         elif workspace.dtype != torch.uint8 or not workspace.is_cuda or \
                 not workspace.is_contiguous():
