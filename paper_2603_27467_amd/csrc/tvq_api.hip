@@ -928,9 +928,9 @@ tvq_status tvq_attention_paged_workspace(const tvq_codec* c, int64_t batch, int3
   return st;
 }
 
-// The shared body of the two attention entry points: `a` holds the cache, its geometry and
-// the paging (if any); t_end bounds every sequence's context.
-static tvq_status attention_launch(const tvq_codec* c, tvq::AttnArgs& a, int64_t batch,
+// The shared body of the two attention entry points: `a` holds the paging (if any); t_end bounds every sequence's context.
+static tvq_status attention_launch(const tvq_codec* c, tvq::AttnArgs& a, const void* cache,
+                                   const tvq_layout* lay, int64_t batch,
                                    int32_t layer, int64_t t_end, int64_t block_tokens,
                                    int32_t num_q_heads, float scale, tvq_dtype q_dtype,
                                    const void* q, tvq_dtype o_dtype, void* o, void* workspace,
@@ -945,21 +945,25 @@ static tvq_status attention_launch(const tvq_codec* c, tvq::AttnArgs& a, int64_t
   AttnPlan p;
   st = attn_plan(c, batch, num_q_heads, t_end, block_tokens, fmt, &p);
   if (st != TVQ_OK) return st;
-  if (!a.cache || !q || !o || !workspace || !aligned16(a.cache) || !aligned16(q) ||
+  if (!cache || !q || !o || !workspace || !aligned16(cache) || !aligned16(q) ||
       !aligned16(o) || !aligned16(workspace) || workspace_bytes < p.ws_bytes)
     return TVQ_ERR_INVALID_ARG;
   if (batch * num_q_heads * p.n_chunks * c->d >= (1ll << 31) ||
       batch * c->H * p.n_chunks * p.n_pass >= (1ll << 31))
     return TVQ_ERR_INVALID_ARG;
-  a.seg[0] = c->segs[2 * layer];
-  a.seg[1] = c->segs[2 * layer + 1];
-  a.sign_masks = c->d_sign_masks;
-  a.lut = c->d_lut;
+  const int64_t n_slots = lay->batch * c->H * lay->capacity_tokens;
+  for (int kind = 0; kind < 2; ++kind) {
+    const tvq::SegParams& sp = c->segs[2 * layer + kind];
+    a.lut[kind] = c->d_lut + 2 * (size_t)sp.lut_off;
+    for (int p = 0; p < 3; ++p)
+      a.plane[kind][p] = (const uint8_t*)cache + n_slots * (int64_t)sp.pre[p];
+  }
+  a.signs = c->d_sign_masks + (size_t)layer * (c->d / 2);
+  a.cap = (uint32_t)lay->capacity_tokens;
   a.q = q;
   a.o = o;
   a.ws_acc = (float*)workspace;
   a.ws_ml = (float*)((char*)workspace + p.acc_bytes);
-  a.layer = (uint32_t)layer;
   a.B = (uint32_t)batch;
   a.H = (uint32_t)c->H;
   a.G = p.G;
@@ -988,10 +992,7 @@ tvq_status tvq_attention_decode(const tvq_codec* c, const void* cache, const tvq
   if (t_end > lay->capacity_tokens) return TVQ_ERR_INVALID_ARG;
   tvq::AttnArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.cache = (const uint8_t*)cache;
-  a.n_slots = lay->batch * c->H * lay->capacity_tokens;
-  a.cap = (uint32_t)lay->capacity_tokens;
-  return attention_launch(c, a, lay->batch, layer, t_end, 0, num_q_heads, scale, q_dtype, q,
+  return attention_launch(c, a, cache, lay, lay->batch, layer, t_end, 0, num_q_heads, scale, q_dtype, q,
                           o_dtype, o, workspace, workspace_bytes, stream);
 }
 
@@ -1025,10 +1026,7 @@ tvq_status tvq_attention_paged(const tvq_codec* c, const void* pool, const tvq_l
   if (!ctx_lens || ((uintptr_t)ctx_lens & 3u) != 0) return TVQ_ERR_INVALID_ARG;
   if (max_ctx > (int64_t)max_blocks * pool_layout->capacity_tokens) return TVQ_ERR_INVALID_ARG;
   a.pg.seq = ctx_lens;
-  a.cache = (const uint8_t*)pool;
-  a.n_slots = pool_layout->batch * c->H * pool_layout->capacity_tokens;
-  a.cap = (uint32_t)pool_layout->capacity_tokens;
-  return attention_launch(c, a, batch, layer, max_ctx, pool_layout->capacity_tokens, num_q_heads,
+  return attention_launch(c, a, pool, pool_layout, batch, layer, max_ctx, pool_layout->capacity_tokens, num_q_heads,
                           scale, q_dtype, q, o_dtype, o, workspace, workspace_bytes, stream);
 }
 

@@ -50,12 +50,6 @@ constexpr float kLazyLog2 = 8.0f;    // weights 2^(s - m) stay below 2^8 between
 // distinct banks
 constexpr int kQPitch = kElemsPerLane + 4;
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-
 // Rotation inside each row of 16 lanes (DPP row_ror: a register operation, no LDS traffic).
 template <int N>
 __device__ __forceinline__ uint32_t row_ror(uint32_t v) {
@@ -64,6 +58,36 @@ __device__ __forceinline__ uint32_t row_ror(uint32_t v) {
 template <int N>
 __device__ __forceinline__ float row_ror(float v) {
   return __uint_as_float(row_ror<N>(__float_as_uint(v)));
+}
+
+// The value of lane ^ B, by register moves (B = 4: the mirror of each half row is lane ^ 7).
+template <int B>
+__device__ __forceinline__ float lane_xor(float v) {
+  static_assert(B == 1 || B == 2 || B == 4 || B == 8, "inside a row of 16 lanes");
+  if constexpr (B == 1) return quad_perm<0xB1>(v);
+  else if constexpr (B == 2) return quad_perm<0x4E>(v);
+  else if constexpr (B == 4) return quad_perm<0x1B>(quad_perm<0x141>(v));
+  else return row_ror<8>(v);
+}
+
+// Maximum and sum over the wave, uniform: the rows by rotations, then their four values.
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, row_ror<8>(v));
+  v = fmaxf(v, row_ror<4>(v));
+  v = fmaxf(v, row_ror<2>(v));
+  v = fmaxf(v, row_ror<1>(v));
+  return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)),
+               fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  v += row_ror<1>(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
 template <int D>
@@ -75,7 +99,6 @@ struct AttnWave {
   uint32_t t0, ntok;             // the wave's tokens [t0, t0 + ntok)
   uint32_t row;                  // cache slot of token 0 of (b, h) (contiguous layout)
   uint32_t blk;                  // paged: lane i holds the pool block of the wave's i-th block
-  const uint8_t* plane[2][3];
 };
 
 // Inclusive prefix sum over the wave's lanes (row shifts inside the rows of 16, then the last
@@ -109,6 +132,7 @@ __device__ __forceinline__ uint32_t span_count(const AttnArgs& a, uint32_t T, ui
 // Columns [first, first + count) of one sequence.
 struct SeqColumns {
   uint32_t b, first, count;
+  uint32_t ctx;                  // the sequence's context
 };
 
 // The columns of sequence `want` (BY_SEQ) or of the sequence that holds column `want`; count 0
@@ -118,7 +142,7 @@ __device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t wa
   constexpr uint32_t VPW = AttnWave<D>::VPW;
   if (!a.pg.seq) {
     const uint32_t b = BY_SEQ ? want : want / a.per_seq;
-    return SeqColumns{b, b * a.per_seq, a.per_seq};
+    return SeqColumns{b, b * a.per_seq, a.per_seq, a.t_end};
   }
   const uint32_t lane = threadIdx.x & (kWave - 1);
   uint32_t total = 0;
@@ -130,7 +154,8 @@ __device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t wa
   uint32_t off = 0;
   for (uint32_t b0 = 0; b0 < a.B; b0 += kWave) {
     const bool in = b0 + lane < a.B;
-    const uint32_t T = in ? (seq_context(a, b0 + lane) + VPW - 1) / VPW : 0u;
+    const uint32_t ctx = in ? seq_context(a, b0 + lane) : 0u;
+    const uint32_t T = (ctx + VPW - 1) / VPW;
     const uint32_t n = in ? span_count(a, T, total) : 0u;
     const uint32_t end = off + wave_scan(n);
     const uint64_t hit = __builtin_amdgcn_ballot_w64(
@@ -139,11 +164,11 @@ __device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t wa
       const int l = __builtin_ctzll(hit);
       const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)n, l);
       return SeqColumns{b0 + (uint32_t)l, (uint32_t)__builtin_amdgcn_readlane((int)end, l) - cnt,
-                        cnt};
+                        cnt, (uint32_t)__builtin_amdgcn_readlane((int)ctx, l)};
     }
     off = (uint32_t)__builtin_amdgcn_readlane((int)end, kWave - 1);
   }
-  return SeqColumns{0, 0, 0};
+  return SeqColumns{0, 0, 0, 0};
 }
 
 template <int KW, int KN, int VW, int VN>
@@ -165,7 +190,7 @@ __device__ __forceinline__ u32x2 v_header(const AttnArgs& a, const AttnWave<D>& 
     const uint32_t tok = w.t0 + j;
     slot = ((blk * a.H + w.h) << a.pg.block_log2) + (tok & ((1u << a.pg.block_log2) - 1u));
   }
-  return *(const u32x2*)(w.plane[1][2] + (uint64_t)slot * 8);
+  return *(const u32x2*)(a.plane[1][2] + (uint64_t)slot * 8);
 }
 
 // The codes of `tile`: this lane's token (vector slot) and slice.  The tile's first token is
@@ -189,14 +214,33 @@ __device__ __forceinline__ TilePair<KW, KN, VW, VN> tile_pair(const AttnArgs& a,
     slot0 = ((blk * a.H + w.h) << a.pg.block_log2) + (tok & ((1u << a.pg.block_log2) - 1u));
   }
   TilePair<KW, KN, VW, VN> p;
-  p.k = load_codes_from<KW, KN>(w.plane[0], a.seg[0].rec, slot0, j, w.sub);
-  p.v = load_codes_from<VW, VN>(w.plane[1], a.seg[1].rec, slot0, j, w.sub);
+  // bytes per vector of the planes
+  const uint32_t rk[3] = {D * KW / 16, D * KN / 16, 8}, rv[3] = {D * VW / 16, D * VN / 16, 8};
+  p.k = load_codes_from<KW, KN>(a.plane[0], rk, slot0, j, w.sub);
+  p.v = load_codes_from<VW, VN>(a.plane[1], rv, slot0, j, w.sub);
   return p;
 }
 
 // The Sylvester butterfly of a vector held EPL = D / 64 consecutive elements per lane, stages in
 // ascending order: element bit 0 inside the lane at d = 128, then the stages over the lane's
 // bits, where the lane with the bit clear keeps a + b and its partner a - b.
+// Bits 4 and 5: the swap of odd rows (upper half) of one copy with even rows (lower half) of the
+// other leaves a in one register and b in the other on both lanes of a pair.
+template <int B>
+__device__ __forceinline__ float fwht_stage(float x, int lane) {
+  const float sgn = (lane & B) ? -1.0f : 1.0f;
+  if constexpr (B < 16) {
+    return __builtin_fmaf(x, sgn, lane_xor<B>(x));
+  } else {
+    const uint32_t u = __float_as_uint(x);
+    const auto ab = [u] {
+      if constexpr (B == 16) return __builtin_amdgcn_permlane16_swap(u, u, false, false);
+      else return __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    }();
+    return __builtin_fmaf(__uint_as_float(ab[1]), sgn, __uint_as_float(ab[0]));
+  }
+}
+
 template <int EPL>
 __device__ __forceinline__ void fwht_across_lanes(float (&x)[EPL], int lane) {
   if constexpr (EPL == 2) {
@@ -205,10 +249,13 @@ __device__ __forceinline__ void fwht_across_lanes(float (&x)[EPL], int lane) {
     x[1] = p - q;
   }
 #pragma unroll
-  for (int b = 1; b < kWave; b <<= 1) {
-    const float sgn = (lane & b) ? -1.0f : 1.0f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) x[e] = __builtin_fmaf(x[e], sgn, __shfl_xor(x[e], b));
+  for (int e = 0; e < EPL; ++e) {
+    float v = fwht_stage<1>(x[e], lane);
+    v = fwht_stage<2>(v, lane);
+    v = fwht_stage<4>(v, lane);
+    v = fwht_stage<8>(v, lane);
+    v = fwht_stage<16>(v, lane);
+    x[e] = fwht_stage<32>(v, lane);
   }
 }
 
@@ -396,7 +443,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   if (sc.count == 0) return;
   w.b = sc.b;
   // the span's tiles, then the wave's: as even as whole tiles allow
-  const uint32_t ctx = seq_context(a, w.b);
+  const uint32_t ctx = sc.ctx;
   const uint32_t tiles = (ctx + VPW - 1) / VPW;
   const uint32_t k = col - sc.first;
   const uint32_t per = tiles / sc.count, extra = tiles - per * sc.count;
@@ -406,17 +453,6 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   w.t0 = nt != 0 ? (span0 + wib * wper + min(wib, wextra)) * VPW : 0u;
   w.ntok = nt != 0 ? min(nt * VPW, ctx - w.t0) : 1u;   // no tile: token 0 is loaded, not used
   w.row = (w.b * a.H + w.h) * a.cap;
-  w.blk = 0;
-  if (a.pg.table) {
-    // lane i: the pool block of the wave's i-th block (entries past the table or naming no
-    // pool block read block 0, so a corrupt table stays inside the pool)
-    const uint32_t i = (w.t0 >> a.pg.block_log2) + (uint32_t)lane;
-    const uint32_t blk = i < a.pg.max_blocks
-                             ? (uint32_t)a.pg.table[(size_t)w.b * a.pg.max_blocks + i] : 0u;
-    w.blk = blk < a.pg.n_blocks ? blk : 0u;
-  }
-  for (int kind = 0; kind < 2; ++kind)
-    for (int p = 0; p < 3; ++p) w.plane[kind][p] = a.cache + a.n_slots * a.seg[kind].pre[p];
   const uint32_t g0 = pass * a.pass_heads;
   const uint32_t gc = min(a.pass_heads, a.G - g0);     // query heads g0 .. g0 + gc - 1
   float* const lds = s_wave[wib];
@@ -433,13 +469,22 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   // this wave, the tables, the first tile's codes and the first V headers
   constexpr int EPL = D / kWave;
   const uint64_t head = (uint64_t)w.b * a.Hq + w.h * a.G + g0 + (wib < gc ? wib : 0u);
-  const uint32_t smw = a.sign_masks[(size_t)a.layer * (D / 2) + (EPL * lane) / 2];
+  const uint32_t smw = a.signs[(EPL * lane) / 2];
   float qx[EPL];
   load_query<D>(a, head * D, lane, qx);
   const uint32_t ek = threadIdx.x & ((1u << KW) - 1u), ev = threadIdx.x & ((1u << VW) - 1u);
-  const float2 tk = ((const float2*)a.lut)[a.seg[0].lut_off + ek];
+  const float2 tk = ((const float2*)a.lut[0])[ek];
   float2 tv;
-  if constexpr (!kShared) tv = ((const float2*)a.lut)[a.seg[1].lut_off + ev];
+  if constexpr (!kShared) tv = ((const float2*)a.lut[1])[ev];
+  w.blk = 0;
+  if (a.pg.table) {
+    // lane i: the pool block of the wave's i-th block (entries past the table or naming no
+    // pool block read block 0, so a corrupt table stays inside the pool)
+    const uint32_t i = (w.t0 >> a.pg.block_log2) + (uint32_t)lane;
+    const uint32_t blk = i < a.pg.max_blocks
+                             ? (uint32_t)a.pg.table[(size_t)w.b * a.pg.max_blocks + i] : 0u;
+    w.blk = blk < a.pg.n_blocks ? blk : 0u;
+  }
   // log-space V norms: the ladder ratio of each token, computed for LPV tiles at once (the LPV
   // lanes of a token would otherwise compute the same one): the lane on slice sl holds that of
   // its token in tile LPV k + sl, and tile LPV k + u reads it from the lane of slice u
@@ -701,7 +746,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
       ax[e] = __builtin_fmaf(s_wave[v][wib * kAccPitch + EPL * lane + e], f, ax[e]);
   }
   if (a.direct) {
-    const uint32_t smo = a.sign_masks[(size_t)a.layer * (D / 2) + (EPL * lane) / 2];
+    const uint32_t smo = a.signs[(EPL * lane) / 2];
     store_output<D>(a, head, ax, M, L, smo, lane);
     return;
   }
@@ -729,10 +774,23 @@ __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
   const uint64_t col0 = (uint64_t)(j - b * a.Hq) * a.n_part + sc.first;
   const float2* const ml = (const float2*)(a.ws_ml + col0 * 2);
   const float* const acc = a.ws_acc + col0 * D + EPL * lane;
-  const uint32_t smw = a.sign_masks[(size_t)a.layer * (D / 2) + (EPL * lane) / 2];
+  const uint32_t smw = a.signs[(EPL * lane) / 2];
+  // the first 64 spans' (m, l) and the first rows are requested before any is used
+  constexpr uint32_t kRows = 16;
+  float2 v = (uint32_t)lane < nc ? ml[lane] : make_float2(-INFINITY, 0.0f);
+  float r[kRows][EPL];
+  auto load_rows = [&](uint32_t c0) {
+#pragma unroll
+    for (uint32_t k = 0; k < kRows; ++k) {
+      const float* src = acc + (size_t)min(c0 + k, nc - 1) * D;     // in bounds; weight 0 below
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) r[k][e] = src[e];
+    }
+  };
+  load_rows(0);
   // M over every span (an empty one carries m = -inf)
-  float M = -INFINITY;
-  for (uint32_t c = (uint32_t)lane; c < nc; c += kWave) M = fmaxf(M, ml[c].x);
+  float M = v.x;
+  for (uint32_t c = (uint32_t)lane + kWave; c < nc; c += kWave) M = fmaxf(M, ml[c].x);
   M = wave_max(M);
   float L = 0.0f;
   float x[EPL];
@@ -740,38 +798,24 @@ __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
   for (int e = 0; e < EPL; ++e) x[e] = 0.0f;
   if (M != -INFINITY) {
     for (uint32_t c0 = 0; c0 < nc; c0 += kWave) {
-      const uint32_t c = c0 + (uint32_t)lane;
-      const float2 v = c < nc ? ml[c] : make_float2(-INFINITY, 0.0f);
+      if (c0 != 0)
+        v = c0 + (uint32_t)lane < nc ? ml[c0 + lane] : make_float2(-INFINITY, 0.0f);
       const float wc = v.x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(v.x - M);
       L = __builtin_fmaf(v.y, wc, L);
       const uint32_t n = min(nc - c0, (uint32_t)kWave);
-      // eight spans' rows requested before any is used
-      for (uint32_t k0 = 0; k0 < n; k0 += 8) {
-        float r[8][EPL];
+      for (uint32_t k0 = 0; k0 < n; k0 += kRows) {
+        if (c0 + k0 != 0) load_rows(c0 + k0);
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-          const uint32_t kk = min(k0 + k, n - 1);            // in bounds; weight 0 below
-          const float* src = acc + (size_t)(c0 + kk) * D;
-          if constexpr (EPL == 2) {
-            const float2 t = *(const float2*)src;
-            r[k][0] = t.x, r[k][1] = t.y;
-          } else {
-            r[k][0] = *src;
-          }
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-          // span c0 + k0 + k's weight, from its lane (a wave-uniform index below 64)
-          const int wk = __builtin_amdgcn_readlane(__float_as_int(wc), (int)min(k0 + k, 63u));
-          const float wf = k0 + k < n ? __int_as_float(wk) : 0.0f;
+        for (uint32_t k = 0; k < kRows; ++k) {
+          // span c0 + k0 + k's weight, from its lane (0 past the last span)
+          const float wf = lane_value(wc, (int)(k0 + k));
 #pragma unroll
           for (int e = 0; e < EPL; ++e) x[e] = __builtin_fmaf(r[k][e], wf, x[e]);
         }
       }
     }
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) L += __shfl_xor(L, o);
+  L = wave_sum(L);
   store_output<D>(a, j, x, M, L, smw, lane);
 }
 

@@ -130,18 +130,12 @@ struct DecodeArgs {
 // at most ceil(T / 4) (a tile per wave) where that is at least c(T), with spare = n_part - B c(T
 // of t_end).  The counts never add up to more than n_part, the spans hold close to the same
 // number of tiles whatever the contexts, and equal contexts share the columns evenly.
+//
+// The fields are what the kernels read and no more: a launch begins with the misses on its
+// arguments' cache lines, which no other wave of the device has touched.
 struct AttnArgs {
-  const uint8_t* cache;
-  int64_t n_slots;       // B * H * capacity
-  uint32_t cap;
-  SegParams seg[2];      // K and V of the layer
-  const uint32_t* sign_masks;
-  const float* lut;      // float2 entries, 1/sqrt(d) folded in
-  const void* q;         // [B][Hq][d]
-  void* o;               // [B][Hq][d]
-  float* ws_acc;         // [Hq][n_part][d]
-  float* ws_ml;          // [Hq][n_part][2]
-  uint32_t layer, B, H, G, Hq;
+  Paging pg;             // pg.seq: context length per sequence (nullptr: t_end for all)
+  uint32_t B, H, G, Hq;
   uint32_t t_end;
   uint32_t n_part;       // columns of partials per query head
   uint32_t per_seq;      // columns of each sequence (pg.seq null)
@@ -151,8 +145,15 @@ struct AttnArgs {
   uint32_t direct;       // every sequence holds one column: the workgroups store the outputs
   uint32_t q_f32;        // query dtype: 1 = fp32, 0 = bf16
   uint32_t o_f32;        // output dtype, likewise
+  uint32_t cap;          // capacity tokens of a contiguous cache
   float qscale;          // scale * log2(e): scores in log2 units
-  Paging pg;             // pg.seq: context length per sequence (nullptr: t_end for all)
+  const void* q;         // [B][Hq][d]
+  const uint32_t* signs; // sign masks of the layer
+  const float* lut[2];   // the layer's K and V tables: float2 entries, 1/sqrt(d) folded in
+  const uint8_t* plane[2][3];   // the layer's planes (angle codes, norm codes, headers) of K, V
+  float* ws_acc;         // [Hq][n_part][d]
+  float* ws_ml;          // [Hq][n_part][2]
+  void* o;               // [B][Hq][d]
 };
 
 constexpr int kAttnPassHeads = 4;           // accumulators of 4 query heads per wave
