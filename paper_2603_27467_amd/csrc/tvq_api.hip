@@ -29,11 +29,10 @@ struct tvq_codec {
   // format (bit 0: 8-bit angle codes, bit 1: 4-bit log norms), and the most over the formats
   int64_t attn_slots[4][4] = {};
   int64_t attn_slots_max = 0;
-  tvq::SegParams* d_segs = nullptr;
+  tvq::SegParams* d_segs = nullptr;          // [2L], fast formats first
   uint32_t* d_sign_masks = nullptr;
   float* d_lut = nullptr;
   uint32_t* d_abins = nullptr;               // angle bins of n = 64, 256, 128 (pairs)
-  uint32_t* d_seg_lists = nullptr;           // fast-format segment ids, then the others
   uint32_t n_mfma = 0, n_fast = 0, n_generic = 0;   // segment list: the first n_mfma of the
                                                     // n_fast also suit tvq_encode_mfma
 };
@@ -510,8 +509,9 @@ tvq_status tvq_create(const tvq_config* cfg, tvq_codec** out) {
   for (uint32_t i = 0; i < c->segs.size(); ++i)
     if (!tvq::fast_format(c->segs[i].n, c->segs[i].mode, c->segs[i].bits)) lists.push_back(i);
   c->n_generic = (uint32_t)lists.size() - c->n_fast;
-  const size_t list_bytes = lists.size() * sizeof(uint32_t);
-  const size_t seg_bytes = c->segs.size() * sizeof(tvq::SegParams);
+  std::vector<tvq::SegParams> ordered;
+  for (uint32_t i : lists) ordered.push_back(c->segs[i]);
+  const size_t seg_bytes = ordered.size() * sizeof(tvq::SegParams);
   const size_t mask_bytes = masks.size() * sizeof(uint32_t);
   const size_t lut_bytes = lut.size() * sizeof(float);
   // angle bins of the fast formats' codebooks, as (code, boundary bits) pairs
@@ -531,16 +531,14 @@ tvq_status tvq_create(const tvq_config* cfg, tvq_codec** out) {
   if (hipMalloc((void**)&c->d_segs, seg_bytes) != hipSuccess ||
       hipMalloc((void**)&c->d_abins, abin_bytes) != hipSuccess ||
       hipMalloc((void**)&c->d_sign_masks, mask_bytes) != hipSuccess ||
-      hipMalloc((void**)&c->d_lut, lut_bytes) != hipSuccess ||
-      hipMalloc((void**)&c->d_seg_lists, list_bytes) != hipSuccess) {
+      hipMalloc((void**)&c->d_lut, lut_bytes) != hipSuccess) {
     tvq_destroy(c);
     return TVQ_ERR_ALLOC;
   }
-  if (hipMemcpy(c->d_segs, c->segs.data(), seg_bytes, hipMemcpyHostToDevice) != hipSuccess ||
+  if (hipMemcpy(c->d_segs, ordered.data(), seg_bytes, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(c->d_sign_masks, masks.data(), mask_bytes, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(c->d_lut, lut.data(), lut_bytes, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(c->d_abins, abins.data(), abin_bytes, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(c->d_seg_lists, lists.data(), list_bytes, hipMemcpyHostToDevice) != hipSuccess) {
+      hipMemcpy(c->d_abins, abins.data(), abin_bytes, hipMemcpyHostToDevice) != hipSuccess) {
     tvq_destroy(c);
     return TVQ_ERR_HIP;
   }
@@ -554,7 +552,6 @@ void tvq_destroy(tvq_codec* c) {
   if (c->d_sign_masks) (void)hipFree(c->d_sign_masks);
   if (c->d_lut) (void)hipFree(c->d_lut);
   if (c->d_abins) (void)hipFree(c->d_abins);
-  if (c->d_seg_lists) (void)hipFree(c->d_seg_lists);
   delete c;
 }
 
@@ -593,7 +590,6 @@ static bool paging_valid(const tvq_codec* c, const tvq_layout* pool, const int32
 // Encode launches over the segment lists; `a` holds the source view and destination.
 static tvq_status encode_launch(const tvq_codec* c, tvq::EncodeArgs& a, const tvq_tensor_desc* in,
                                 bool f32, void* stream) {
-  a.segs = c->d_segs;
   a.sign_masks = c->d_sign_masks;
   a.abins = c->d_abins;
   a.div_t = make_div((uint32_t)in->tokens);
@@ -610,7 +606,7 @@ static tvq_status encode_launch(const tvq_codec* c, tvq::EncodeArgs& a, const tv
       {n_fast, c->n_fast + c->n_generic - n_fast, 1, false}};
   for (const auto& l : launches) {
     if (l.count == 0) continue;
-    a.seg_list = c->d_seg_lists + l.first;
+    a.segs = c->d_segs + l.first;
     a.num_segs = l.count;
     a.has_n128 = l.fast && l.count > c->n_mfma ? 1u : 0u;
     const unsigned grid = plan_tiles(
@@ -731,7 +727,6 @@ static tvq_status decode_launch(const tvq_codec* c, tvq::DecodeArgs& a,
   a.stride_b = (uint32_t)out->stride_b;
   a.stride_h = (uint32_t)out->stride_h;
   a.stride_t = (uint32_t)out->stride_t;
-  a.segs = c->d_segs;
   a.sign_masks = c->d_sign_masks;
   a.lut = c->d_lut;
   a.div_t = make_div((uint32_t)out->tokens);
@@ -748,7 +743,7 @@ static tvq_status decode_launch(const tvq_codec* c, tvq::DecodeArgs& a,
       {n_fast, c->n_fast + c->n_generic - n_fast, 1, false}};
   for (const auto& l : launches) {
     if (l.count == 0) continue;
-    a.seg_list = c->d_seg_lists + l.first;
+    a.segs = c->d_segs + l.first;
     a.num_segs = l.count;
     const unsigned grid = plan_tiles(
         a, l.fast && (uint64_t)a.stride_t * vpw * (out_dtype == TVQ_F32 ? 4u : 2u) < (1ull << 31),

@@ -148,7 +148,7 @@ __device__ __forceinline__ bool wave_setup(const DecodeArgs& a, WaveState<D>& w,
   tile0 = wseg * a.tiles_per_wave;
   if (tile0 >= a.seg_tiles) return false;
   ntiles = min(a.tiles_per_wave, a.seg_tiles - tile0);
-  w.sp = a.segs[a.seg_list[li]];
+  w.sp = a.segs[li];
   for (int p = 0; p < 3; ++p) w.plane[p] = a.cache + a.n_slots * w.sp.pre[p];
   w.lut_g = (const float2*)a.lut + w.sp.lut_off;
   w.lut_s = nullptr;

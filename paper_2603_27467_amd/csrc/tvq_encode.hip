@@ -308,7 +308,7 @@ __device__ __forceinline__ bool enc_wave_setup(const EncodeArgs& a, EncWave<D>& 
   tile0 = wseg * a.tiles_per_wave;
   if (tile0 >= a.seg_tiles) return false;
   ntiles = min(a.tiles_per_wave, a.seg_tiles - tile0);
-  w.sp = a.segs[a.seg_list[li]];
+  w.sp = a.segs[li];
   w.src = w.sp.kind ? a.v : a.k;
   w.layer_off = (int64_t)w.sp.layer * a.stride_l + w.sub * kElemsPerLane;
   w.lane_in_bytes = (uint32_t)(w.sub * kElemsPerLane + w.vslot * a.stride_t) * 2u;

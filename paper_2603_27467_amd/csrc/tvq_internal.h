@@ -1,7 +1,8 @@
 // tvq_internal.h -- structures shared by the host side of libtvq and its gfx950 kernels.
 //
 // Data layout of the device tables built by tvq_create:
-//   SegParams  [2L]        one per (layer, kind), index 2*layer + kind (0 = K, 1 = V)
+//   SegParams  [2L]        one per (layer, kind), those of one launch side by side, so that a
+//                          wave finds its segment with one load after its arguments
 //   sign masks [L][d/2]    u32 XOR masks of the sign diagonal D for element pairs (2m, 2m+1)
 //                          of a bf16 word: bit 15 flips element 2m, bit 31 flips element 2m+1
 //   trig LUT   sum_s n_s   float2 (cos, sin)(2 pi k / n) / sqrt(d) per codebook (each value
@@ -69,8 +70,7 @@ struct EncodeArgs {
   int64_t n_slots;      // B * H * capacity, below 2^31
   uint32_t cap;         // capacity tokens
   uint32_t t_begin;
-  const SegParams* segs;
-  const uint32_t* seg_list;  // segment indices this launch covers
+  const SegParams* segs;  // the segments this launch covers
   const uint32_t* sign_masks;
   const uint32_t* abins;  // angle bins (code, boundary) of n = 64 (2 x 64), 256, 128
   FastDiv div_t, div_h;  // by T (tokens in the call) and by H
@@ -97,8 +97,7 @@ struct DecodeArgs {
   int64_t n_slots;      // below 2^31
   uint32_t cap;
   uint32_t t_begin;
-  const SegParams* segs;
-  const uint32_t* seg_list;  // segment indices this launch covers
+  const SegParams* segs;  // the segments this launch covers
   const uint32_t* sign_masks;
   const float* lut;      // float2 entries
   FastDiv div_t, div_h;
