@@ -25,7 +25,7 @@ struct tvq_codec {
   uint64_t rec_total = 0;                    // record bytes of all planes, per slot
   int device = 0;
   void* scratch = nullptr;                   // the static attention scratch on `device`
-  // chunk waves of the attention the device holds at once (d = 64, 128), per key and value
+  // waves of the attention kernel that the device holds at once (d = 64, 128), per key and value
   // format (bit 0: 8-bit angle codes, bit 1: 4-bit log norms), and the most over the formats
   int64_t attn_slots[4][4] = {};
   int64_t attn_slots_max = 0;
