@@ -192,7 +192,8 @@ tvq_status tvq_decode(const tvq_codec* c, const void* cache, const tvq_layout* l
  * created on.
  * tvq_attention_workspace names no layer and gives the size for the formats with the most
  * chunks, which covers every layer.  Query heads are processed up to 4 per pass over the
- * codes (G > 4 reads them ceil(G/4) times).  Arithmetic is fp32 (expect ~1e-5 relative to an fp64 evaluation).
+ * codes (G > 4 reads them ceil(G/4) times).  Arithmetic is fp32 (expect ~1e-5 relative to an
+ * fp64 evaluation).
  * Supported: d = 64 or 128, G <= 64, and for both K and V of the layer n = 64 or 256 with
  * 8-bit linear or 4-bit log-space norms (TVQ_ERR_UNSUPPORTED otherwise).  Launches two
  * kernels on `stream`, one where every sequence is a single span. */
@@ -211,11 +212,11 @@ tvq_status tvq_attention_decode(const tvq_codec* c, const void* cache, const tvq
 
 /* tvq_attention_decode without the workspace argument, for callers that cannot allocate
  * device memory (code under graph capture, serving loops that forbid allocation): the
- * per-chunk partials go to the library's static scratch on the codec's device.  Allocates
+ * per-span partials go to the library's static scratch on the codec's device.  Allocates
  * nothing and calls no allocating routine; arguments, results and launches are those of
  * tvq_attention_decode.  TVQ_ERR_SCRATCH, with nothing launched, when the call's partials
- * (the chunks planned for this layer's formats) exceed TVQ_ATTENTION_SCRATCH_BYTES; TVQ_ERR_HIP when the scratch's
- * device address could not be obtained at tvq_create.  Every call on one GPU shares that
+ * (the workspace size for this layer's formats) exceed TVQ_ATTENTION_SCRATCH_BYTES; TVQ_ERR_HIP
+ * when the scratch's device address could not be obtained at tvq_create.  Every call on one GPU shares that
  * scratch: calls that overlap in time on one GPU (concurrent streams, or host threads each
  * launching) race on it and must be ordered by the caller.  The scratch needs no clearing:
  * each call writes every partial it reads. */

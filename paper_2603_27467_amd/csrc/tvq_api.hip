@@ -224,7 +224,7 @@ unsigned plan_grid(uint64_t tiles_per_seg, uint32_t num_segs, uint32_t* waves_pe
 // a tile boundary on).
 template <class Args>
 unsigned plan_tiles(Args& a, bool row_ok, uint64_t rows, uint64_t tokens, uint64_t span,
-                           uint32_t vpw, uint32_t max_tiles_per_wave) {
+                    uint32_t vpw, uint32_t max_tiles_per_wave) {
   const uint64_t per_row = (span + vpw - 1) / vpw;
   a.rows = 0;
   if (row_ok && tvq::row_tiles(tokens, per_row, vpw, a.pg.table != nullptr)) {
@@ -619,8 +619,8 @@ static tvq_status encode_launch(const tvq_codec* c, tvq::EncodeArgs& a, const tv
   return TVQ_OK;
 }
 
-// Contiguous ranges of at least this many vectors per kind whose token count is not a multiple of the
-// tile's are encoded or decoded in two parts (whole tiles per (batch, head) row, on the
+// Contiguous ranges of at least this many vectors per kind whose token count is not a multiple
+// of the tile's are encoded or decoded in two parts (whole tiles per (batch, head) row, on the
 // kernels that keep a tile's position in scalar registers, then the remaining tokens of every
 // row): below it the extra launch costs more than those kernels save.
 constexpr int64_t kSplitVectors = 1 << 19;
@@ -923,7 +923,8 @@ tvq_status tvq_attention_paged_workspace(const tvq_codec* c, int64_t batch, int3
   return st;
 }
 
-// The shared body of the two attention entry points: `a` holds the paging (if any); t_end bounds every sequence's context.
+// The shared body of the two attention entry points: `a` holds the paging (if any); t_end bounds
+// every sequence's context.
 static tvq_status attention_launch(const tvq_codec* c, tvq::AttnArgs& a, const void* cache,
                                    const tvq_layout* lay, int64_t batch,
                                    int32_t layer, int64_t t_end, int64_t block_tokens,
@@ -1021,8 +1022,9 @@ tvq_status tvq_attention_paged(const tvq_codec* c, const void* pool, const tvq_l
   if (!ctx_lens || ((uintptr_t)ctx_lens & 3u) != 0) return TVQ_ERR_INVALID_ARG;
   if (max_ctx > (int64_t)max_blocks * pool_layout->capacity_tokens) return TVQ_ERR_INVALID_ARG;
   a.pg.seq = ctx_lens;
-  return attention_launch(c, a, pool, pool_layout, batch, layer, max_ctx, pool_layout->capacity_tokens, num_q_heads,
-                          scale, q_dtype, q, o_dtype, o, workspace, workspace_bytes, stream);
+  return attention_launch(c, a, pool, pool_layout, batch, layer, max_ctx,
+                          pool_layout->capacity_tokens, num_q_heads, scale, q_dtype, q, o_dtype, o,
+                          workspace, workspace_bytes, stream);
 }
 
 double tvq_bits_per_element_config(const tvq_config* cfg, int accounting) {
