@@ -290,15 +290,15 @@ __device__ __forceinline__ void load_query(const AttnArgs& a, uint64_t elem, int
   }
 }
 
-// o = D W (A / L) of output j, its elements EPL lane .. on the lanes; no token at all (M = -inf)
-// gives zeros.
+// o = D W (A / L) of output j, its elements EPL lane .. on the lanes; no token with a score above
+// -inf (M = -inf: no token at all, or every score NaN, which leaves A NaN) gives zeros.
 template <int D>
 __device__ __forceinline__ void store_output(const AttnArgs& a, uint64_t j, float (&x)[D / kWave],
                                              float M, float L, uint32_t smw, int lane) {
   constexpr int EPL = D / kWave;
-  const float inv = M == -INFINITY ? 0.0f : 1.0f / L;
+  const float inv = 1.0f / L;
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) x[e] *= inv;
+  for (int e = 0; e < EPL; ++e) x[e] = M == -INFINITY ? 0.0f : x[e] * inv;
   fwht_across_lanes<EPL>(x, lane);
   apply_signs<EPL>(x, smw, lane);
   const uint64_t elem = j * D + EPL * lane;

@@ -126,3 +126,26 @@ def test_attention_spans(gpu, d, H, G, max_ctx, block, lens):
             check(got, n, b)
         if b < 6:
             check(got_full, max_ctx, b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T", [40, 3000])
+def test_query_head_of_nan(gpu, d, T):
+    """A query head of NaN has no score above -inf and gives zeros, like an empty context, with one
+    span per sequence (T = 40: the workgroups store the outputs) as with several (the merge does);
+    the other heads of its pass are what they are without it."""
+    import torch
+    B, H, G = 2, 2, 4
+    s = Setup(1, H, d, [LayerCfg(64, 64)], workloads.sign_table(31, 1, d)).build()
+    k, v = _draw(workloads.get("C2"), 1, B, H, T, d, "bf16", 32)
+    lay = s.gpu.layout(B, T)
+    cache = torch.zeros((lay.total_bytes,), dtype=torch.uint8, device="cuda")
+    s.gpu.encode(bf16_bits_to_torch(k).cuda(), bf16_bits_to_torch(v).cuda(), cache, lay)
+    q = torch.randn((B, H * G, d), generator=torch.Generator("cuda").manual_seed(7), device="cuda")
+    want, got = torch.empty_like(q), torch.empty_like(q)
+    s.gpu.attention(cache, lay, 0, T, q, want, d ** -0.5)
+    q[1, 5] = float("nan")
+    s.gpu.attention(cache, lay, 0, T, q, got, d ** -0.5)
+    want[1, 5] = 0
+    assert torch.isfinite(want).all() and torch.equal(got, want)
