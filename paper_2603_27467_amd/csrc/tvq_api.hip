@@ -896,9 +896,12 @@ static tvq_status attn_plan(const tvq_codec* c, int64_t batch, int32_t num_q_hea
   // equal contexts: per_seq columns each; contexts on the device: the remainder is shared too
   const int64_t n_part = equal ? batch * per_seq
                                : std::max(batch * need, std::min(per_head, batch * most));
-  p->per_seq = (uint32_t)per_seq;
-  p->n_part = (uint32_t)n_part;
-  p->spare = (uint32_t)(n_part - batch * need);
+  // with nothing to share every sequence has the columns of a full context; so too past the
+  // batch that the lookup of shared columns holds
+  const bool share = !equal && n_part > batch * need && batch <= tvq::kMaxSpareBatch;
+  p->per_seq = (uint32_t)(equal ? per_seq : need);
+  p->n_part = (uint32_t)(equal || share ? n_part : batch * need);
+  p->spare = (uint32_t)(share ? n_part - batch * need : 0);
   p->max_span = (uint32_t)max_span;
   return TVQ_OK;
 }

@@ -123,8 +123,11 @@ __device__ __forceinline__ uint32_t seq_context(const AttnArgs& a, uint32_t b) {
 // span_count of AttnArgs for a sequence of T tiles, `total` tiles in all.  T * spare is exact in
 // fp64 (spare is at most the workgroups of a launch), and its quotient cannot round up to an
 // integer above it, so the counts add up to at most n_part.
+__device__ __forceinline__ uint32_t span_floor(const AttnArgs& a, uint32_t T) {
+  return T <= a.max_span ? 1u : (T + a.max_span - 1) / a.max_span;
+}
 __device__ __forceinline__ uint32_t span_count(const AttnArgs& a, uint32_t T, uint32_t total) {
-  const uint32_t c = T <= a.max_span ? 1u : (T + a.max_span - 1) / a.max_span;
+  const uint32_t c = span_floor(a, T);
   const uint32_t more = (uint32_t)((double)T * (double)a.spare / (double)total);
   return max(c, min(c + more, (T + kWavesPerBlock - 1) / kWavesPerBlock));
 }
@@ -135,40 +138,58 @@ struct SeqColumns {
   uint32_t ctx;                  // the sequence's context
 };
 
-// The columns of sequence `want` (BY_SEQ) or of the sequence that holds column `want`; count 0
-// when no sequence does.  Uniform; every lane of the wave takes part.
+// The columns of sequence `want` (BY_SEQ), or of the sequence whose columns (column) `want` lies
+// in or, with no spare columns, behind; count 0 when there is none.  Uniform; every lane of the
+// wave takes part.  With spare columns lane i looks after k consecutive sequences, k = ceil(B / 64):
+// their tiles are added up, then their columns, and where k > 1 the sequences of the lane that
+// holds `want` are looked up one per lane: the lookup adds up over the wave two or three times,
+// whatever the batch.
 template <int D, bool BY_SEQ>
 __device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t want) {
   constexpr uint32_t VPW = AttnWave<D>::VPW;
-  if (!a.pg.seq) {
+  if (a.spare == 0) {
     const uint32_t b = BY_SEQ ? want : want / a.per_seq;
-    return SeqColumns{b, b * a.per_seq, a.per_seq, a.t_end};
+    const uint32_t ctx = seq_context(a, b);
+    const uint32_t n = a.pg.seq ? span_floor(a, (ctx + VPW - 1) / VPW) : a.per_seq;
+    return SeqColumns{b, b * a.per_seq, n, ctx};
   }
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  uint32_t total = 0;
-  for (uint32_t b0 = 0; b0 < a.B; b0 += kWave) {
-    const uint32_t T = b0 + lane < a.B ? (seq_context(a, b0 + lane) + VPW - 1) / VPW : 0u;
-    total += (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(T), kWave - 1);
+  const uint32_t k = (a.B + kWave - 1) / kWave;
+  auto context = [&](uint32_t b) { return b < a.B ? seq_context(a, b) : 0u; };
+  auto read = [](uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+  uint32_t b = lane, ctx = 0, T = 0;
+  if (k == 1) {
+    ctx = context(lane);
+    T = (ctx + VPW - 1) / VPW;
+  } else {
+#pragma unroll 4
+    for (uint32_t j = 0; j < k; ++j) T += (context(lane * k + j) + VPW - 1) / VPW;
   }
-  total = max(total, 1u);
-  uint32_t off = 0;
-  for (uint32_t b0 = 0; b0 < a.B; b0 += kWave) {
-    const bool in = b0 + lane < a.B;
-    const uint32_t ctx = in ? seq_context(a, b0 + lane) : 0u;
-    const uint32_t T = (ctx + VPW - 1) / VPW;
-    const uint32_t n = in ? span_count(a, T, total) : 0u;
-    const uint32_t end = off + wave_scan(n);
+  const uint32_t total = max(read(wave_scan(T), kWave - 1), 1u);
+  auto columns = [&](uint32_t s, uint32_t c) {
+    return s < a.B ? span_count(a, (c + VPW - 1) / VPW, total) : 0u;
+  };
+  uint32_t base = 0;
+  if (k > 1) {
+    uint32_t n = 0;
+#pragma unroll 4
+    for (uint32_t j = 0; j < k; ++j) n += columns(lane * k + j, context(lane * k + j));
+    const uint32_t end = wave_scan(n);
     const uint64_t hit = __builtin_amdgcn_ballot_w64(
-        in && (BY_SEQ ? b0 + lane == want : want >= end - n && want < end));
-    if (hit != 0) {
-      const int l = __builtin_ctzll(hit);
-      const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)n, l);
-      return SeqColumns{b0 + (uint32_t)l, (uint32_t)__builtin_amdgcn_readlane((int)end, l) - cnt,
-                        cnt, (uint32_t)__builtin_amdgcn_readlane((int)ctx, l)};
-    }
-    off = (uint32_t)__builtin_amdgcn_readlane((int)end, kWave - 1);
+        BY_SEQ ? lane == want / k : want >= end - n && want < end);
+    if (hit == 0) return SeqColumns{0, 0, 0, 0};
+    const int l = __builtin_ctzll(hit);
+    base = read(end - n, l);
+    b = lane < k ? (uint32_t)l * k + lane : a.B;
+    ctx = context(b);
   }
-  return SeqColumns{0, 0, 0, 0};
+  const uint32_t n = columns(b, ctx);
+  const uint32_t end = base + wave_scan(n);
+  const uint64_t hit =
+      __builtin_amdgcn_ballot_w64(BY_SEQ ? b == want : want >= end - n && want < end);
+  if (hit == 0) return SeqColumns{0, 0, 0, 0};
+  const int l = __builtin_ctzll(hit);
+  return SeqColumns{read(b, l), read(end - n, l), read(n, l), read(ctx, l)};
 }
 
 template <int KW, int KN, int VW, int VN>
@@ -440,7 +461,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   w.h = unit / a.n_part;
   const uint32_t col = unit - w.h * a.n_part;
   const SeqColumns sc = seq_columns<D, false>(a, col);
-  if (sc.count == 0) return;
+  if (col - sc.first >= sc.count) return;
   w.b = sc.b;
   // the span's tiles, then the wave's: as even as whole tiles allow
   const uint32_t ctx = sc.ctx;

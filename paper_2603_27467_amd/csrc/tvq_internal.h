@@ -122,10 +122,11 @@ struct DecodeArgs {
 // the spans of a sequence.
 //
 // The spans of the sequences are the n_part columns of one list per head: sequence b holds
-// span_count(T_b) consecutive columns, T_b its tiles, in batch order.  With every context equal
-// (pg.seq null) that is per_seq columns each; otherwise the contexts are device data and every
-// workgroup counts the same way:
-//   span_count(T) = c(T) + floor(T * spare / sum_b T_b),   c(T) = max(1, ceil(T / max_span)),
+// consecutive columns in batch order, T_b its tiles:
+//   spare == 0  per_seq columns each, of which it uses all (pg.seq null: the contexts are equal) or
+//               c(T_b) = max(1, ceil(T_b / max_span)), nothing to look up but its own context;
+//   spare > 0   (contexts on the device) span_count(T_b) columns, counted by every workgroup alike:
+//   span_count(T) = c(T) + floor(T * spare / sum_b T_b),
 // at most ceil(T / 4) (a tile per wave) where that is at least c(T), with spare = n_part - B c(T
 // of t_end).  The counts never add up to more than n_part, the spans hold close to the same
 // number of tiles whatever the contexts, and equal contexts share the columns evenly.
@@ -137,7 +138,7 @@ struct AttnArgs {
   uint32_t B, H, G, Hq;
   uint32_t t_end;
   uint32_t n_part;       // columns of partials per query head
-  uint32_t per_seq;      // columns of each sequence (pg.seq null)
+  uint32_t per_seq;      // columns of each sequence (spare 0)
   uint32_t spare;        // columns shared by context length (pg.seq not null)
   uint32_t max_span;     // most tiles of a workgroup's span
   uint32_t pass_heads, n_pass;  // query heads per workgroup (<= kAttnPassHeads), passes over G
@@ -157,6 +158,7 @@ struct AttnArgs {
 
 constexpr int kAttnPassHeads = 4;           // accumulators of 4 query heads per wave
 constexpr uint32_t kAttnMaxGroup = 64;      // query heads per KV head
+constexpr int64_t kMaxSpareBatch = 4096;    // sequences that share columns: 64 per lane
 // Formats of the attention kernels and of the matrix-core encode: n = 64 or 256 (6- or 8-bit
 // angle codes, every code a valid bin) with 8-bit linear or 4-bit log-space norms.
 inline bool attn_format(uint32_t n, uint32_t mode, uint32_t bits) {

@@ -70,8 +70,10 @@ def test_span_counts_fit_the_columns():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,H,G,max_ctx,block,lens", [
-    # more sequences than a wave has lanes; empty, one-token and tile-edge contexts
+    # more sequences than a wave has lanes (two, five a lane); empty, one-token and tile-edge
+    # contexts
     (128, 1, 4, 300, 32, [0, 1, 15, 16, 17, 300, 63, 64, 65] + [33] * 70),
+    (128, 2, 4, 600, 32, [600, 0, 17, 64] * 72 + [1, 600, 599]),
     (64, 2, 3, 300, 64, [0, 1, 31, 32, 33, 300, 127, 128, 129] + [5] * 62),
     # every context one span: the workgroups store the outputs themselves
     (128, 2, 8, 64, 32, [64, 0, 1, 40]),
