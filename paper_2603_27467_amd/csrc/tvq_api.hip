@@ -2,7 +2,8 @@
 //
 // tvq_create validates the configuration and uploads three small device tables (segment
 // parameters, sign masks, cos/sin lookup); tvq_encode / tvq_decode validate their arguments
-// on the host and enqueue exactly one kernel each, with no allocation and no synchronization.
+// on the host and enqueue their kernels (tvq.h states how many), with no allocation and no
+// synchronization.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -15,6 +16,7 @@
 
 #include "../../include/tvq.h"
 #include "tvq_internal.h"
+#include "tvq_spans.h"
 
 struct tvq_codec {
   int32_t L = 0, H = 0, d = 0;
@@ -824,24 +826,9 @@ tvq_status tvq_decode_paged(const tvq_codec* c, const void* pool, const tvq_layo
   return decode_launch(c, a, out, out_dtype, k_out, v_out, stream);
 }
 
-// Tokens per chunk of the workspace rule: the rows (sequence, KV head, pass over the query
-// heads) split into equal chunks so that there is about one per wave slot of the device
-// (`slots`).  A chunk holds whole tile pairs, at least four tiles, and at most `max_chunk`
-// tokens.  The workspace holds a partial per query head and chunk; the launch's spans (one per
-// workgroup of four waves) never number more.
-static uint32_t attn_chunk_tokens(int d, int64_t rows, int64_t t_end, int64_t slots,
-                                  int64_t max_chunk) {
-  const int64_t vpw = tvq::kWave / (d / tvq::kElemsPerLane);
-  const int64_t step = 2 * vpw;
-  const int64_t per_row = std::max<int64_t>(1, slots / rows);
-  int64_t ch = (t_end + per_row - 1) / per_row;
-  ch = std::max<int64_t>((ch + step - 1) / step * step, 4 * vpw);
-  return (uint32_t)std::min(ch, max_chunk / step * step);
-}
-
 struct AttnPlan {
-  uint32_t G, pass_heads, n_pass, chunk, n_chunks;
-  uint32_t n_part, per_seq, spare, max_span;       // spans (see AttnArgs)
+  uint32_t G, pass_heads, n_pass;
+  tvq::AttnSplit split;
   int64_t acc_bytes, ws_bytes;
 };
 
@@ -856,14 +843,11 @@ static tvq_status attn_formats(const tvq_codec* c, int32_t layer, int (&fmt)[2])
   return TVQ_OK;
 }
 
-// block_tokens: 0 for the contiguous layout, else the pool's block size (a chunk then spans
-// at most 64 blocks, one per lane of the wave that fetches their pool indices, and the
-// contexts are device data).  fmt: the
-// layer's formats, or nullptr for the plan with the most chunks over the formats (the
-// workspace queries, which name no layer: a layer's plan never has more chunks).
+// block_tokens: 0 for the contiguous layout, else the pool's block size.  fmt: the layer's
+// formats, or nullptr for the plan with the most chunks over the formats (the workspace queries,
+// which name no layer: a layer's plan never has more chunks).
 static tvq_status attn_plan(const tvq_codec* c, int64_t batch, int32_t num_q_heads,
                             int64_t t_end, int64_t block_tokens, const int* fmt, AttnPlan* p) {
-  const bool equal = block_tokens == 0;     // every context is t_end (the paged ones are device data)
   if (!c || batch < 1 || t_end < 1 || num_q_heads < c->H || num_q_heads % c->H != 0)
     return TVQ_ERR_INVALID_ARG;
   if (c->d != 64 && c->d != 128) return TVQ_ERR_UNSUPPORTED;
@@ -871,38 +855,12 @@ static tvq_status attn_plan(const tvq_codec* c, int64_t batch, int32_t num_q_hea
   if (p->G > tvq::kAttnMaxGroup) return TVQ_ERR_UNSUPPORTED;
   p->n_pass = (p->G + tvq::kAttnPassHeads - 1) / tvq::kAttnPassHeads;
   p->pass_heads = (p->G + p->n_pass - 1) / p->n_pass;          // balanced passes
-  // paged: a chunk may start inside a block, so 63 blocks' tokens keep it within the 64
-  // blocks whose pool indices one wave fetches
-  const int64_t max_chunk = block_tokens > 0 ? std::min<int64_t>(4096, 63 * block_tokens) : 4096;
   const int64_t slots = fmt ? c->attn_slots[fmt[0]][fmt[1]] : c->attn_slots_max;
-  p->chunk = attn_chunk_tokens(c->d, batch * c->H * p->n_pass, t_end, slots, max_chunk);
-  p->n_chunks = (uint32_t)((t_end + p->chunk - 1) / p->chunk);
-  const int64_t parts = batch * num_q_heads * (int64_t)p->n_chunks;
+  p->split = tvq::attn_split(batch, c->H, p->n_pass, t_end, block_tokens,
+                             tvq::kWave / (c->d / tvq::kElemsPerLane), slots);
+  const int64_t parts = batch * num_q_heads * p->split.n_chunks;
   p->acc_bytes = (parts * c->d * 4 + 255) / 256 * 256;
   p->ws_bytes = p->acc_bytes + parts * 2 * 4;
-
-  // Spans: one workgroup of four waves each, as many as the device holds at once, and at least
-  // a tile per wave.  `max_chunk` bounds a wave (a paged wave holds its pool blocks' ids in its
-  // 64 lanes).
-  const int64_t vpw = tvq::kWave / (c->d / tvq::kElemsPerLane);
-  const int64_t tiles = (t_end + vpw - 1) / vpw;
-  const int64_t max_span = tvq::kWavesPerBlock * (max_chunk / vpw);
-  const int64_t need = (tiles + max_span - 1) / max_span;          // columns of a full context
-  const int64_t most = std::min<int64_t>((tiles + tvq::kWavesPerBlock - 1) / tvq::kWavesPerBlock,
-                                         p->n_chunks);
-  const int64_t slots_wg = slots / tvq::kWavesPerBlock;
-  const int64_t per_head = slots_wg / (c->H * p->n_pass);          // columns of one head
-  const int64_t per_seq = std::max(need, std::min(per_head / batch, most));
-  // equal contexts: per_seq columns each; contexts on the device: the remainder is shared too
-  const int64_t n_part = equal ? batch * per_seq
-                               : std::max(batch * need, std::min(per_head, batch * most));
-  // with nothing to share every sequence has the columns of a full context; so too past the
-  // batch that the lookup of shared columns holds
-  const bool share = !equal && n_part > batch * need && batch <= tvq::kMaxSpareBatch;
-  p->per_seq = (uint32_t)(equal ? per_seq : need);
-  p->n_part = (uint32_t)(equal || share ? n_part : batch * need);
-  p->spare = (uint32_t)(share ? n_part - batch * need : 0);
-  p->max_span = (uint32_t)max_span;
   return TVQ_OK;
 }
 
@@ -947,8 +905,8 @@ static tvq_status attention_launch(const tvq_codec* c, tvq::AttnArgs& a, const v
   if (!cache || !q || !o || !workspace || !aligned16(cache) || !aligned16(q) ||
       !aligned16(o) || !aligned16(workspace) || workspace_bytes < p.ws_bytes)
     return TVQ_ERR_INVALID_ARG;
-  if (batch * num_q_heads * p.n_chunks * c->d >= (1ll << 31) ||
-      batch * c->H * p.n_chunks * p.n_pass >= (1ll << 31))
+  if (batch * num_q_heads * p.split.n_chunks * c->d >= (1ll << 31) ||
+      batch * c->H * p.split.n_chunks * p.n_pass >= (1ll << 31))
     return TVQ_ERR_INVALID_ARG;
   const int64_t n_slots = lay->batch * c->H * lay->capacity_tokens;
   for (int kind = 0; kind < 2; ++kind) {
@@ -968,13 +926,14 @@ static tvq_status attention_launch(const tvq_codec* c, tvq::AttnArgs& a, const v
   a.G = p.G;
   a.Hq = (uint32_t)num_q_heads;
   a.t_end = (uint32_t)t_end;
-  a.n_part = p.n_part;
-  a.per_seq = p.per_seq;
-  a.spare = p.spare;
-  a.max_span = p.max_span;
+  a.n_part = (uint32_t)p.split.n_part;
+  a.per_seq = (uint32_t)p.split.per_seq;
+  a.spare = (uint32_t)p.split.spare;
+  a.max_span = (uint32_t)p.split.max_span;
+  a.min_log2 = (uint32_t)p.split.min_log2;
   a.pass_heads = p.pass_heads;
   a.n_pass = p.n_pass;
-  a.direct = p.n_part == (uint32_t)batch ? 1u : 0u;
+  a.direct = p.split.n_part == batch ? 1u : 0u;
   a.q_f32 = q_dtype == TVQ_F32 ? 1u : 0u;
   a.o_f32 = o_dtype == TVQ_F32 ? 1u : 0u;
   a.qscale = scale * 1.4426950408889634f;          // scores in log2 units

@@ -14,11 +14,9 @@
 //
 // Split over tokens (split-K): a workgroup takes a span of whole tiles of one (sequence, KV
 // head) for up to four of the G query heads (G > 4 runs in passes of balanced size), its four
-// waves as even a share each as whole tiles allow.  The spans number about as many as the
-// device holds workgroups, and hold the same number of tiles to within one, also where the
-// contexts differ and are known to the device only (AttnArgs): the launch ends when its longest
-// wave does.  8 sequences of 1025 to 4101 tokens, 8 KV heads, 32 query heads, d = 128: 24 us a
-// layer, 33 us with chunks cut from the longest context (1736 of 4096 waves had work).
+// waves as even a share each as whole tiles allow.  The spans of a sequence hold the same number
+// of tiles to within one, those of different sequences up to the share that tvq_spans.h states,
+// also where the contexts differ and are known to the device only.
 //   prologue  q^_g = scale * log2(e) * W D q_g into LDS, one head per wave; the loads that the
 //             first tile needs are issued before any of them is waited for
 //   per tile  y'_K from the K codes, the scores s_g = q^_g . y'_K, then y'_V from the V codes
@@ -40,6 +38,7 @@
 #include "tvq_codes.h"
 #include "tvq_device.h"
 #include "tvq_internal.h"
+#include "tvq_spans.h"
 
 namespace tvq {
 namespace {
@@ -49,6 +48,7 @@ constexpr float kLazyLog2 = 8.0f;    // weights 2^(s - m) stay below 2^8 between
 // 16-byte reads of a wave (one per lane of a vector, broadcast over the vector slots) fall in
 // distinct banks
 constexpr int kQPitch = kElemsPerLane + 4;
+static_assert(kSpanWaves == kWavesPerBlock, "a span is a workgroup's");
 
 // Rotation inside each row of 16 lanes (DPP row_ror: a register operation, no LDS traffic).
 template <int N>
@@ -120,18 +120,6 @@ __device__ __forceinline__ uint32_t seq_context(const AttnArgs& a, uint32_t b) {
   return len <= 0 ? 0u : min((uint32_t)len, a.t_end);
 }
 
-// span_count of AttnArgs for a sequence of T tiles, `total` tiles in all.  T * spare is exact in
-// fp64 (spare is at most the workgroups of a launch), and its quotient cannot round up to an
-// integer above it, so the counts add up to at most n_part.
-__device__ __forceinline__ uint32_t span_floor(const AttnArgs& a, uint32_t T) {
-  return T <= a.max_span ? 1u : (T + a.max_span - 1) / a.max_span;
-}
-__device__ __forceinline__ uint32_t span_count(const AttnArgs& a, uint32_t T, uint32_t total) {
-  const uint32_t c = span_floor(a, T);
-  const uint32_t more = (uint32_t)((double)T * (double)a.spare / (double)total);
-  return max(c, min(c + more, (T + kWavesPerBlock - 1) / kWavesPerBlock));
-}
-
 // Columns [first, first + count) of one sequence.
 struct SeqColumns {
   uint32_t b, first, count;
@@ -150,7 +138,7 @@ __device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t wa
   if (a.spare == 0) {
     const uint32_t b = BY_SEQ ? want : want / a.per_seq;
     const uint32_t ctx = seq_context(a, b);
-    const uint32_t n = a.pg.seq ? span_floor(a, (ctx + VPW - 1) / VPW) : a.per_seq;
+    const uint32_t n = a.pg.seq ? span_floor((ctx + VPW - 1) / VPW, a.max_span) : a.per_seq;
     return SeqColumns{b, b * a.per_seq, n, ctx};
   }
   const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -167,7 +155,7 @@ __device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t wa
   }
   const uint32_t total = max(read(wave_scan(T), kWave - 1), 1u);
   auto columns = [&](uint32_t s, uint32_t c) {
-    return s < a.B ? span_count(a, (c + VPW - 1) / VPW, total) : 0u;
+    return s < a.B ? span_count((c + VPW - 1) / VPW, total, a.spare, a.max_span, a.min_log2) : 0u;
   };
   uint32_t base = 0;
   if (k > 1) {

@@ -121,15 +121,7 @@ struct DecodeArgs {
 // 2^(s - m) and the accumulated rotated-domain value vector acc[d]; the merge kernel combines
 // the spans of a sequence.
 //
-// The spans of the sequences are the n_part columns of one list per head: sequence b holds
-// consecutive columns in batch order, T_b its tiles:
-//   spare == 0  per_seq columns each, of which it uses all (pg.seq null: the contexts are equal) or
-//               c(T_b) = max(1, ceil(T_b / max_span)), nothing to look up but its own context;
-//   spare > 0   (contexts on the device) span_count(T_b) columns, counted by every workgroup alike:
-//   span_count(T) = c(T) + floor(T * spare / sum_b T_b),
-// at most ceil(T / 4) (a tile per wave) where that is at least c(T), with spare = n_part - B c(T
-// of t_end).  The counts never add up to more than n_part, the spans hold close to the same
-// number of tiles whatever the contexts, and equal contexts share the columns evenly.
+// The spans of the sequences are the n_part columns of one list per head (tvq_spans.h).
 //
 // The fields are what the kernels read and no more: a launch begins with the misses on its
 // arguments' cache lines, which no other wave of the device has touched.
@@ -141,6 +133,7 @@ struct AttnArgs {
   uint32_t per_seq;      // columns of each sequence (spare 0)
   uint32_t spare;        // columns shared by context length (pg.seq not null)
   uint32_t max_span;     // most tiles of a workgroup's span
+  uint32_t min_log2;     // spare columns leave spans of at least 2^min_log2 tiles
   uint32_t pass_heads, n_pass;  // query heads per workgroup (<= kAttnPassHeads), passes over G
   uint32_t direct;       // every sequence holds one column: the workgroups store the outputs
   uint32_t q_f32;        // query dtype: 1 = fp32, 0 = bf16
@@ -158,7 +151,6 @@ struct AttnArgs {
 
 constexpr int kAttnPassHeads = 4;           // accumulators of 4 query heads per wave
 constexpr uint32_t kAttnMaxGroup = 64;      // query heads per KV head
-constexpr int64_t kMaxSpareBatch = 4096;    // sequences that share columns: 64 per lane
 // Formats of the attention kernels and of the matrix-core encode: n = 64 or 256 (6- or 8-bit
 // angle codes, every code a valid bin) with 8-bit linear or 4-bit log-space norms.
 inline bool attn_format(uint32_t n, uint32_t mode, uint32_t bits) {
@@ -210,7 +202,7 @@ constexpr uint32_t kNormSpreadMaxBits = 126u << 23;
 }  // namespace tvq
 
 // Kernel launchers (defined in the .hip kernel files).
-// `a.pg.table` selects the paged instantiations (decode: the generic kernel only).
+// `a.pg.table` selects the paged instantiations.
 int tvq_launch_encode(const tvq::EncodeArgs& a, int d, int in_f32, bool fast, unsigned grid,
                       void* stream);
 int tvq_launch_decode(const tvq::DecodeArgs& a, int d, int out_f32, bool fast, unsigned grid,

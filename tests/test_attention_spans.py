@@ -1,7 +1,11 @@
-"""How an attention call is split: the columns (workgroup spans) of sequences whose contexts are
-device data, by a model of the rule on the CPU, and on the GPU at the contexts where it can go
-wrong, against fp64 attention over the decoded cache."""
+"""How an attention call is split into columns (workgroup spans): the shipped arithmetic compiled
+for the CPU over random calls, and on the GPU the contexts where it can go wrong, against fp64
+attention over the decoded cache."""
+import ctypes
 import math
+import os
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -10,47 +14,57 @@ import workloads
 from parity import Setup, bf16_bits_to_torch
 from test_gpu_parity import LayerCfg, _draw
 
-
-def _plan(d, B, H, n_pass, max_ctx, block, slots=4096):
-    """The plan of a paged call: (tiles per context, n_part, spare, max_span, chunk columns)."""
-    vpw = 64 // (d // 32)
-    max_chunk = min(4096, 63 * block)
-    step = 2 * vpw
-    per_row = max(1, slots // (B * H * n_pass))
-    ch = max(-(-(-(-max_ctx // per_row)) // step) * step, 4 * vpw)
-    ch = min(ch, max_chunk // step * step)
-    n_chunks = -(-max_ctx // ch)
-    tiles = -(-max_ctx // vpw)
-    max_span = 4 * (max_chunk // vpw)
-    need = -(-tiles // max_span)
-    most = min(-(-tiles // 4), n_chunks)
-    n_part = max(B * need, min(slots // 4 // (H * n_pass), B * most))
-    return n_part, n_part - B * need, max_span, n_chunks
+NATIVE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "native", "attn_spans.cpp")
 
 
-def _counts(T, spare, max_span):
-    total = max(int(T.sum()), 1)
-    c = np.maximum(1, -(-T // max_span))
-    more = (T.astype(np.float64) * np.float64(spare) / np.float64(total)).astype(np.int64)
-    return np.maximum(c, np.minimum(c + more, -(-T // 4)))
+class Split:
+    FIELDS = ("chunk", "n_chunks", "n_part", "per_seq", "spare", "max_span", "min_log2")
+
+    def __init__(self, so):
+        self.lib = ctypes.CDLL(so)
+        self.lib.split.argtypes = [ctypes.c_int64] * 7 + [ctypes.c_void_p]
+        self.lib.counts.argtypes = [ctypes.c_void_p, ctypes.c_int64] + [ctypes.c_uint32] * 3 + \
+            [ctypes.c_void_p]
+
+    def plan(self, *args):
+        out = np.zeros(7, np.int64)
+        self.lib.split(*args, out.ctypes.data)
+        return dict(zip(self.FIELDS, (int(x) for x in out)))
+
+    def counts(self, tiles, p):
+        tiles, out = np.ascontiguousarray(tiles, np.uint32), np.zeros(len(tiles), np.uint32)
+        self.lib.counts(tiles.ctypes.data, len(tiles), p["spare"], p["max_span"], p["min_log2"],
+                        out.ctypes.data)
+        return out.astype(np.int64)
 
 
-def test_span_counts_fit_the_columns():
-    """Random batches, heads, passes, block sizes and contexts (zero, equal, one long among
-    short, up to the bound): the counts never exceed the columns, nor the columns the workspace
-    rule's partials; every wave's share is within what it can address; equal contexts share the
-    columns evenly."""
+@pytest.fixture(scope="module")
+def spans(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("g++ not found")
+    so = str(tmp_path_factory.mktemp("spans") / "spans.so")
+    subprocess.run([cxx, "-O2", "-std=c++17", "-shared", "-fPIC", "-o", so, NATIVE], check=True)
+    return Split(so)
+
+
+def test_columns_fit(spans):
+    """Random batches, heads, passes, block sizes, contexts (zero, equal, one long among short,
+    up to the bound) and devices: every sequence has a column, the counts never exceed the columns
+    nor the columns the workspace's partials, no sequence holds more columns than it has tiles,
+    every wave's share is within what it can address, and spans are as even as tvq_spans.h
+    states."""
     rng = np.random.default_rng(1)
-    for case in range(4000):
-        d = (64, 128)[case % 2]
-        vpw = 64 // (d // 32)
-        B = int(math.exp(rng.uniform(0, math.log(300))))
+    for case in range(6000):
+        vpw = (32, 16)[case % 2]
+        B = int(math.exp(rng.uniform(0, math.log(6000))))
         H, n_pass = int(rng.choice([1, 2, 4, 8, 32])), int(rng.integers(1, 17))
-        block = 32 << int(rng.integers(0, 12))
+        block = 0 if case % 5 == 0 else 32 << int(rng.integers(0, 12))
         max_ctx = int(math.exp(rng.uniform(0, math.log(300000))))
-        n_part, spare, max_span, n_chunks = _plan(d, B, H, n_pass, max_ctx, block)
-        assert B <= n_part <= B * n_chunks and spare >= 0
-        kind = case % 4
+        slots = int(rng.choice([256, 3072, 4096, 4864]))
+        p = spans.plan(B, H, n_pass, max_ctx, block, vpw, slots)
+        assert B <= p["n_part"] <= B * p["n_chunks"] and p["spare"] >= 0
+        kind = 1 if block == 0 else case % 4
         lens = rng.integers(0, max_ctx + 1, B)
         if kind == 1:
             lens[:] = max_ctx
@@ -60,12 +74,42 @@ def test_span_counts_fit_the_columns():
         elif kind == 3:
             lens[:] = 0
         T = -(-lens // vpw)
-        n = _counts(T, spare, max_span)
-        assert n.min() >= 1 and n.sum() <= n_part
-        share = -(-(-(-T // n)) // 4)                   # most tiles of a wave
-        assert (share * vpw <= min(4096, 63 * block)).all()
-        if kind == 1 and T[0] // 4 >= n_part // B:
-            assert (n == n_part // B).all()
+        if block == 0:
+            assert p["spare"] == 0 and p["n_part"] == B * p["per_seq"]
+            n = np.full(B, p["per_seq"])
+        else:
+            n = spans.counts(T, p)
+            if p["spare"] == 0:
+                assert p["n_part"] == B * p["per_seq"] and n.max() <= p["per_seq"]
+            else:
+                assert B <= 4096
+        assert n.min() >= 1 and n.sum() <= p["n_part"] and (n <= np.maximum(T, 1)).all()
+        span = -(-T // n)
+        assert (-(-span // 4) * vpw <= min(4096, 63 * block or 4096)).all()
+        if p["spare"]:
+            total = int(T.sum())
+            assert (span <= max(1 << p["min_log2"], -(-total // p["spare"]))).all()
+
+
+@pytest.mark.parametrize("B,H,n_pass", [(33, 8, 1), (49, 8, 1), (65, 8, 1), (72, 8, 1), (98, 8, 1),
+                                        (129, 8, 1), (160, 8, 1), (33, 8, 2), (13, 8, 2),
+                                        (17, 32, 1), (3, 8, 1), (16, 8, 1)])
+@pytest.mark.parametrize("block", [0, 256])
+def test_rows_that_do_not_divide_the_device(spans, B, H, n_pass, block):
+    """4,096-token contexts on a device of 1,024 workgroups: a compute unit's share of the work,
+    placed four workgroups at a time as places fall free, is never 1.15 times that of a wave per
+    chunk of the workspace rule (four waves on the fullest of its SIMDs, in whole chunks): what
+    that split spends on waves of its own for the tables and the partials."""
+    p = spans.plan(B, H, n_pass, 4096, block, 16, 4096)
+    T = 256
+    c = int(spans.counts(np.full(B, T), p)[0]) if block else p["per_seq"]
+    rows, units = B * H * n_pass, 256
+    span = -(-T // c)
+    groups = rows * c
+    # at most one go: the fullest unit's whole spans; more: an even share and a last span alone
+    load = -(-groups // units) * span if groups <= 1024 else groups / units * span + span
+    chunks = -(-rows * p["n_chunks"] // 1024) * (p["chunk"] // 16) * 4
+    assert load <= 1.15 * chunks, (p, load, chunks)
 
 
 @pytest.mark.gpu
