@@ -53,7 +53,8 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
 # unchanged
 CODEC_SOURCES = ["tvq_encode.hip", "tvq_decode.hip", "tvq_codes.h", "tvq_device.h",
                  "tvq_internal.h"]
-ATTENTION_SOURCES = ["tvq_attention.hip", "tvq_codes.h", "tvq_device.h", "tvq_internal.h"]
+ATTENTION_SOURCES = ["tvq_attention.hip", "tvq_codes.h", "tvq_device.h", "tvq_internal.h",
+                     "tvq_spans.h"]
 # the attention counter summary of each workload the attention step runs on
 ATTENTION_COUNTER_FILES = {"C5": "longctx_c5_attention_counters.json",
                            "C4": "d64_batch8_c4_attention_counters.json"}

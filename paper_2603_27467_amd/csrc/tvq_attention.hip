@@ -446,8 +446,8 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   if (unit >= a.n_part * a.H) return;
   AttnWave<D> w;
   w.lane = lane;
-  w.h = unit / a.n_part;
-  const uint32_t col = unit - w.h * a.n_part;
+  w.h = unit_head(unit, a.H);
+  const uint32_t col = unit_column(unit, a.H);
   const SeqColumns sc = seq_columns<D, false>(a, col);
   if (col - sc.first >= sc.count) return;
   w.b = sc.b;
@@ -894,7 +894,7 @@ int tvq_attention_blocks_per_cu(int d, int k_format, int v_format) {
 int tvq_launch_attention(const tvq::AttnArgs& a, int d, int k_format, int v_format,
                          void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  // units (KV head, column) go round the XCDs in eights, the passes of one eight in turn
+  // units (column, KV head) go round the XCDs in eights, the passes of one eight in turn
   const uint64_t units = (uint64_t)a.H * a.n_part;
   const dim3 grid1((unsigned)((units + 7) / 8 * 8 * a.n_pass));
   const uint64_t merge_waves = (uint64_t)a.B * a.Hq;

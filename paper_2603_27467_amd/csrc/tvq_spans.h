@@ -47,6 +47,15 @@ TVQ_HOST_DEVICE uint32_t span_count(uint32_t T, uint32_t total, uint32_t spare, 
   return n > c ? n : c;
 }
 
+// Workgroup `unit` (passes aside) takes KV head unit % heads of column unit / heads: the columns of
+// a long sequence then lie side by side over all XCDs and compute units.  Ordered by head first,
+// the heads' columns of a sequence were n_part apart, a multiple of the XCDs and of an XCD's
+// places as a rule, and met on the same compute units.  8 KV heads, d = 128, us a layer, heads
+// first / columns first: 2 sequences of 8,192 tokens among 126 of 1,000, a column each 442 / 264;
+// 4 of 8,192 among 512 506 / 330; 16 of 8,193 to 32,770 222 / 201; 64 of 75 to 300 26 / 19.
+TVQ_HOST_DEVICE uint32_t unit_column(uint32_t unit, uint32_t heads) { return unit / heads; }
+TVQ_HOST_DEVICE uint32_t unit_head(uint32_t unit, uint32_t heads) { return unit % heads; }
+
 struct AttnSplit {
   int64_t chunk, n_chunks;                       // of the workspace rule
   int64_t n_part, per_seq, spare, max_span, min_log2;
@@ -68,6 +77,11 @@ struct AttnSplit {
 // workspace rule, which four waves of a workgroup make coarser:
 //   equal contexts of 4,096 tokens: 65 sequences 188 / 160 (chunks 163), 98: 235 / 226 (229),
 //   129: 331 / 297 (335); of 1,500 tokens: 65 sequences 74 / 64 (68); of 512: 65 sequences 29 / 30
+//   paged, 65 sequences of 4,096: 198 / 164 (166), 96: 221 / 230 (229)
+//   paged, 1,025 to 4,100 tokens: 24 sequences 44 / 47 (68), 48: 89 / 80 (107), 64: 117 / 103 (142),
+//   100: 164 / 160 (202)
+//   paged, a column a sequence / and a half: 128 of 1,025 to 4,100 186 / 190 (244), 128 of 4,096
+//   275 / 279 (290), 2 of 8,192 and 126 of 1,000 264 / 102 (258)
 inline AttnSplit attn_split(int64_t batch, int64_t heads, int64_t n_pass, int64_t t_end,
                             int64_t block_tokens, int64_t vpw, int64_t slots) {
   AttnSplit s;

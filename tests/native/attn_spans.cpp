@@ -19,3 +19,8 @@ extern "C" void counts(const uint32_t* tiles, int64_t batch, uint32_t spare, uin
     out[b] = spare == 0 ? tvq::span_floor(tiles[b], max_span)
                         : tvq::span_count(tiles[b], total, spare, max_span, min_log2);
 }
+
+extern "C" void unit(uint32_t u, uint32_t heads, uint32_t* column_and_head) {
+  column_and_head[0] = tvq::unit_column(u, heads);
+  column_and_head[1] = tvq::unit_head(u, heads);
+}

@@ -23,6 +23,7 @@ class Split:
     def __init__(self, so):
         self.lib = ctypes.CDLL(so)
         self.lib.split.argtypes = [ctypes.c_int64] * 7 + [ctypes.c_void_p]
+        self.lib.unit.argtypes = [ctypes.c_uint32] * 2 + [ctypes.c_void_p]
         self.lib.counts.argtypes = [ctypes.c_void_p, ctypes.c_int64] + [ctypes.c_uint32] * 3 + \
             [ctypes.c_void_p]
 
@@ -30,6 +31,11 @@ class Split:
         out = np.zeros(7, np.int64)
         self.lib.split(*args, out.ctypes.data)
         return dict(zip(self.FIELDS, (int(x) for x in out)))
+
+    def unit(self, u, heads):
+        out = np.zeros(2, np.uint32)
+        self.lib.unit(u, heads, out.ctypes.data)
+        return int(out[0]), int(out[1])
 
     def counts(self, tiles, p):
         tiles, out = np.ascontiguousarray(tiles, np.uint32), np.zeros(len(tiles), np.uint32)
@@ -110,6 +116,18 @@ def test_rows_that_do_not_divide_the_device(spans, B, H, n_pass, block):
     load = -(-groups // units) * span if groups <= 1024 else groups / units * span + span
     chunks = -(-rows * p["n_chunks"] // 1024) * (p["chunk"] // 16) * 4
     assert load <= 1.15 * chunks, (p, load, chunks)
+
+
+@pytest.mark.parametrize("H", [1, 2, 8, 32])
+def test_units_of_a_sequence_are_neighbours(spans, H):
+    """Every (column, head) has one unit, and the units of a column are consecutive, so that one
+    long sequence's workgroups go round the XCDs and their compute units."""
+    n_part = 129
+    units = [spans.unit(u, H) for u in range(n_part * H)]
+    assert sorted(units) == [(c, h) for c in range(n_part) for h in range(H)]
+    for c in range(n_part):
+        at = [u for u, (col, _) in enumerate(units) if col == c]
+        assert at == list(range(at[0], at[0] + H))
 
 
 @pytest.mark.gpu
