@@ -261,7 +261,7 @@ def _bins_code(code, bound, n, a, b, rcp_ulps=0):
     return k.astype(np.int64), entry
 
 
-@pytest.mark.parametrize("n", [16, 64, 256])
+@pytest.mark.parametrize("n", [16, 64, 128, 256])
 def test_angle_bins_reproduce_the_angle_code(tvq, orc, n):
     """The angle bins of the fast encode kernels (p' = sign(a) b / (|a| + |b|), a cell of
     [-1, 1] per sign of a, the code at the cell's low edge plus one past its boundary) give
