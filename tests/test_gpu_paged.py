@@ -330,13 +330,13 @@ def test_paged_multi_tile(gpu, d, T):
     kernels): 4 layers of the common formats, 4 sequences of 2 heads written from positions
     0, 5, 32 and 300 (tiles that start inside a block and tiles that straddle two), 256-slot
     blocks in a shuffled order, one missing block inside sequence 3's range and spare blocks.
-    T a multiple of the tile's vector count gives the tiles of one (batch, head) row (input
-    addressed once per tile), the odd T tiles that cross rows.  Checks: every code and header
-    against the oracle's encode of the same tokens at the same positions, pool blocks no table
-    names untouched; the decode of the whole table range (a multiple of the tile's count from 0:
-    one block lookup per tile) in fp32 and bf16 against the oracle's fp64 decode on the written
-    positions, zeros without a block; a window starting inside a tile (per-lane lookups) equal to
-    the whole-range decode bit for bit."""
+    Every (batch, head) row is cut into tiles of its own (input addressed once per tile); with the
+    odd T the last of a row is short.  Checks: every code and header against the oracle's encode of
+    the same tokens at the same positions, pool blocks no table names untouched; the decode of the
+    whole table range (whole tiles from 0, one block lookup per tile) in fp32 and bf16 against the
+    oracle's fp64 decode on the written positions, zeros without a block; a window starting inside
+    a tile (a first and a last tile of part of their vectors) equal to the whole-range decode bit
+    for bit.  Tiles that cross rows: test_ragged_rows_and_n128."""
     import torch
     L, B, Pb = 4, 4, 256
     fmt = [LayerCfg(64, 64), LayerCfg(256, 256), LayerCfg(64, 256), LayerCfg(256, 64)]
@@ -389,11 +389,12 @@ def test_paged_multi_tile(gpu, d, T):
     assert np.array_equal(gw.view(np.uint32), full[torch.float32][..., t0:t1, :].view(np.uint32))
 
 
-def test_paged_decode_large_ragged_split(gpu):
+def test_paged_decode_large_ragged(gpu):
     """A paged decode of 2^19 + whole-tile vectors per kind whose token count is not a multiple
     of the tile's (1 layer, 4 sequences x 8 KV heads x 16389 tokens in 256-slot shuffled
-    blocks): decoded as whole tiles per row, then the 5 remaining tokens of every row.  The
-    result equals the two parts decoded by separate calls bit for bit, and sampled vectors (the
+    blocks): one launch of row tiles, the last of a row of 5 vectors.  The result equals that of
+    separate calls for the whole tiles and the remaining 5 tokens of every row bit for bit, and
+    sampled vectors (the
     last tokens of every row, 400 random ones) meet the decode bars against the oracle's fp64
     decode of the gathered records."""
     import torch
@@ -414,7 +415,7 @@ def test_paged_decode_large_ragged_split(gpu):
     shape = (L, B, H, T, d)
     ko = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
     vo = torch.full_like(ko, float("nan"))
-    s.gpu.decode_paged(pool, pool_lay, table_dev, 0, T, ko, vo)              # split inside
+    s.gpu.decode_paged(pool, pool_lay, table_dev, 0, T, ko, vo)
     k2, v2 = torch.full_like(ko, float("nan")), torch.full_like(ko, float("nan"))
     for t0, t1 in ((0, whole), (whole, T)):                                    # two calls
         s.gpu.decode_paged(pool, pool_lay, table_dev, t0, t1, k2[..., t0:t1, :], v2[..., t0:t1, :])
@@ -432,7 +433,7 @@ def test_paged_decode_large_ragged_split(gpu):
         for t in picks:
             ref64 = s.orc.decode_cache(gath, 1, cap, t, t + 1, "f64")[:, :, 0]
             check_decoded(chk, ref64, d, g32=g[:, :, b, :, t:t + 1])
-    _say(f"[paged split] {chk.line()}")
+    _say(f"[paged large ragged] {chk.line()}")
     assert chk.ok()
 
 

@@ -523,26 +523,50 @@ def test_multi_tile_encode_sampled(gpu, d, L, B, T, t_begin, pad):
     assert stats["hdr_ulp"] <= 2
 
 
-@pytest.mark.parametrize("d,L,B,T,t_begin,pad", [
-    (128, 2, 4, 4112, 5, 0),     # whole tiles per (batch, head) row, two tiles per wave
-    (128, 2, 4, 4101, 3, 0),     # row tiles, the last one of 5 vectors
-    (128, 2, 4, 4111, 15, 32),   # the last one lacks a vector; strided views
-    (128, 4, 56, 135, 16, 0),    # short rows, 8.4 tiles: cut into tiles of their own
-    (128, 4, 56, 129, 1, 0),     # too short for that (8.1 tiles): packed tiles
-    (64, 2, 4, 8197, 0, 0),
-    (64, 2, 4, 8223, 31, 16),
-    (64, 2, 1, 33, 2, 0),        # one tile per wave, a tile of one vector
+def _tile_plan(rows, tokens, first, vpw, segments, paged):
+    """The host's tiles of an encode or decode launch of the common formats (at least two tiles
+    per wave: "rows" cut into tiles of their own, "packed" ones that cross rows; else "single") and
+    the tiles of a wave: 256 CUs x 32 waves before tiles are grouped, at most four to a wave.
+    `first`: the first token's offset in its tile (paged decode)."""
+    per_row = -(-(tokens + first) // vpw)
+    by_row = per_row * vpw * 8 <= tokens * 9 if paged else tokens % vpw == 0
+    for kind, tiles in (("rows", rows * per_row), ("packed", -(-rows * tokens // vpw))):
+        n = min(4, max(1, tiles * segments // (256 * 32)))
+        if n > 1 and (kind == "packed" or by_row):
+            return kind, n
+    return "single", 1
+
+
+@pytest.mark.parametrize("d,L,B,T,t_begin,pad,encode,decode", [
+    # whole tiles per (batch, head) row, two tiles per wave, from off a tile boundary
+    (128, 2, 4, 4112, 5, 0, ("rows", 2), ("rows", 2)),
+    (128, 2, 4, 4101, 3, 0, ("rows", 2), ("rows", 2)),      # the last tile of a row of 5 vectors
+    (128, 2, 4, 4111, 15, 32, ("rows", 2), ("rows", 2)),    # it lacks a vector; strided views
+    (128, 4, 60, 135, 16, 0, ("rows", 2), ("rows", 2)),     # short rows, 8.4 tiles
+    (128, 4, 74, 113, 1, 0, ("packed", 2), ("packed", 2)),  # too short for row tiles (7.1 of 8)
+    (128, 4, 74, 113, 1, 8, ("packed", 2), ("packed", 2)),  # the same through strided views
+    (64, 2, 4, 8197, 0, 0, ("rows", 2), ("rows", 2)),
+    (64, 2, 4, 8223, 31, 16, ("rows", 2), ("rows", 2)),
+    # more than two tiles per wave: a second group of ladder ratios and a second record register
+    (64, 4, 88, 270, 7, 0, ("rows", 3), ("rows", 3)),
+    (64, 4, 116, 270, 0, 0, ("rows", 4), ("rows", 4)),
+    (64, 4, 74, 226, 3, 0, ("packed", 2), ("packed", 2)),
+    (64, 2, 1, 33, 2, 0, ("single", 1), ("single", 1)),     # a tile of one vector
 ])
-def test_ragged_rows_and_n128(gpu, d, L, B, T, t_begin, pad):
+def test_ragged_rows_and_n128(gpu, d, L, B, T, t_begin, pad, encode, decode):
     """The tiles of multi-tile launches at their edges (row tiles whose last one is short, from
     cache positions off a tile boundary, and packed ones), with n = 128 (7-bit codes: 14-byte
     chunks, odd lanes starting between dwords) and both norm modes, contiguous and through a
     pool in shuffled blocks, from and into views of token stride d + pad: codes and headers of
     the last tiles of every segment and of 600 random vectors against the oracle's encode, slots
-    outside the range untouched, and the decoded values of those vectors (fp32 and bf16) against
-    the oracle's decode of the bytes."""
+    outside the range untouched, the decoded values of those vectors (fp32 and bf16) against the
+    oracle's decode of the bytes, and the decode of a sequence's records laid out as a contiguous
+    cache bit for bit that from the pool.  `encode` and `decode`: the tiles of the pool's calls."""
     import torch
     H = 4 if T > 100 else 2
+    vpw = 64 // (d // 32)
+    assert _tile_plan(B * H, T, 0, vpw, 2 * L, True) == encode
+    assert _tile_plan(B * H, T, t_begin % vpw, vpw, 2 * L, True) == decode
     table = [LayerCfg(128, 128), LayerCfg(64, 128), LayerCfg(256, 64), LayerCfg(64, 64)][:L]
     w = workloads.get("C2")
     s = Setup(L, H, d, table, workloads.sign_table(17, L, d)).build()
@@ -576,8 +600,17 @@ def test_ragged_rows_and_n128(gpu, d, L, B, T, t_begin, pad):
     host = torch_to_np(cache)
     assert untouched_outside(host, s, B, T, T_cap, t_begin, 0xAB)
     gath = [gather_paged(torch_to_np(pool), s, B * per, bt, order[b], 0) for b in range(B)]
+    one = s.gpu.layout(1, per * bt)
+    for b in sorted({0, B - 1}):
+        flat = torch.from_numpy(gath[b]).cuda()
+        for dt in (torch.float32, torch.bfloat16):
+            ko = torch.full((L, 1, H, T, d), float("nan"), dtype=dt, device="cuda")
+            vo = torch.full_like(ko, float("nan"))
+            s.gpu.decode(flat, one, t_begin, t_begin + T, ko, vo)
+            for got, want in zip((ko, vo), pouts[dt]):
+                assert np.array_equal(torch_to_np(got)[:, 0].view(np.uint8),
+                                      np.ascontiguousarray(want[:, b]).view(np.uint8))
     nvec = B * H * T
-    vpw = 64 // (d // 32)
     rng = np.random.default_rng(4)
     picks = [(l, kind, j) for l in range(L) for kind in range(2)
              for j in range(max(0, (nvec - 1) // vpw - 2) * vpw, nvec)]
@@ -896,15 +929,17 @@ def test_attention_random_formats_and_shapes(gpu):
 
 @pytest.mark.parametrize("d,T", [(128, 4480), (64, 8960)])
 def test_attention_many_chunks(gpu, d, T):
-    """Contexts split into more than 64 chunks per (sequence, KV head), so the merge takes
-    the chunks' partials in several groups of 64 (2 sequences x 2 KV heads on a device of
-    ~4096 wave slots: 64-token chunks at d = 128, 128-token chunks at d = 64)."""
+    """Contexts split into more than 64 spans per (sequence, KV head), so the merge takes the
+    spans' partials in several groups of 64: 2 sequences x 2 KV heads leave a device of more than
+    256 workgroups a span per 4 tiles (a tile per wave), 70 of them.  The workspace, a partial per
+    chunk of 4 tiles, bounds the spans from above."""
     s, lay, cache, q = _attention_case(d, 4, T, [LayerCfg(64, 64), LayerCfg(256, 64)], seed=61)
     B, Hq = q.shape[0], q.shape[1]
     ws = s.gpu.attention_workspace_bytes(B, Hq, T)
     n_chunks = ws // (B * Hq * (4 * d + 8))
-    _say(f"[attn many chunks d={d}] {n_chunks} chunks per output")
-    assert n_chunks > 64
+    tiles = -(-T // (64 // (d // 32)))
+    _say(f"[attn many chunks d={d}] {-(-tiles // 4)} spans, {n_chunks} chunks per output")
+    assert 64 < -(-(tiles - 3) // 4) and -(-tiles // 4) <= n_chunks
     for t_end in (T, T - 37):
         _attention_check(s, lay, cache, q, 1, t_end, 1.0 / np.sqrt(d), f"attn chunks d={d}")
 
