@@ -153,7 +153,9 @@ tvq_status tvq_encode(const tvq_codec* c, tvq_dtype in_dtype, const void* k, con
  * the other three stages follow in registers.  Every stage of W is applied, but not in the
  * canonical ascending order, so a code can differ from tvq_encode's where rounding moves the
  * angle or norm coordinate across a bin boundary (inside the 1e-6-of-range flag zone of the
- * parity rule); other layers are encoded as by tvq_encode.  TVQ_ERR_UNSUPPORTED for d != 128. */
+ * parity rule); other layers are encoded by the kernel of the remaining formats, which for n = 128
+ * gives tvq_encode's codes but inside that zone (tvq_encode takes its angle codes from a table
+ * where a call has several tiles per wave).  TVQ_ERR_UNSUPPORTED for d != 128. */
 tvq_status tvq_encode_mfma(const tvq_codec* c, const void* k, const void* v,
                            const tvq_tensor_desc* in, int64_t t_begin, void* cache,
                            const tvq_layout* lay, void* stream);

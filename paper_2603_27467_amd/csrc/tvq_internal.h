@@ -175,9 +175,15 @@ constexpr uint32_t kFastTilesPerWave = 4;
 // Contiguous: where the rows are whole tiles.  Ragged rows gain nothing (8 heads, d = 128, 32
 // layers: encode of 1999 tokens 95 us either way, of 2 x 4097 tokens 318 us packed and 346 us in
 // row tiles, whose rows start at any multiple of 256 bytes).
-// Paged: also ragged ones, whose last tile is short, where that adds at most 1/8 to the work
-// (encode / decode of 8 x 300 tokens 118 -> 108 / 113 -> 95 us, of 16 x 120 tokens, 1/15 more
-// work, 97 -> 91 / 90 -> 80 us).
+// Paged: also ragged ones, whose last tile is short, where that adds at most 1/8 to the work.  The
+// line is the encode's; 16 layers of 8 heads, some 120,000 tokens, row tiles / packed, us at
+// work added of
+//   d = 128  0.06: 319/333   0.12: 334/336   0.13: 333/332   0.15: 338/334   0.19: 344/334
+//            0.31: 367/338   0.46: 398/341
+//   d = 64   0.06: 167/170   0.08: 169/173   0.12: 177/181   0.14: 194/191   0.19: 182/179
+//            0.24: 192/178   0.48: 211/182
+// The decode, with one block lookup per tile, would gain beyond it (d = 128: 0.13 293/324,
+// 0.23 302/332, 0.31 315/330, 0.46 338/337; d = 64: 0.24 159/178, 0.32 165/182, 0.48 177/187).
 inline bool row_tiles(uint64_t tokens, uint64_t tiles, uint64_t vpw, bool paged) {
   return paged ? tiles * vpw * 8 <= tokens * 9 : tokens % vpw == 0;
 }

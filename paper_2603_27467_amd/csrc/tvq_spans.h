@@ -78,8 +78,8 @@ struct AttnSplit {
 //   equal contexts of 4,096 tokens: 65 sequences 188 / 160 (chunks 163), 98: 235 / 226 (229),
 //   129: 331 / 297 (335); of 1,500 tokens: 65 sequences 74 / 64 (68); of 512: 65 sequences 29 / 30
 //   paged, 65 sequences of 4,096: 198 / 164 (166), 96: 221 / 230 (229)
-//   paged, 1,025 to 4,100 tokens: 24 sequences 44 / 47 (68), 48: 89 / 80 (107), 64: 117 / 103 (142),
-//   100: 164 / 160 (202)
+//   paged, 1,025 to 4,100 tokens: 33 sequences 60 / 63 (80), 40: 70 / 69 (83), 48: 89 / 80 (107),
+//   64: 117 / 103 (142), 100: 164 / 160 (202)
 //   paged, a column a sequence / and a half: 128 of 1,025 to 4,100 186 / 190 (244), 128 of 4,096
 //   275 / 279 (290), 2 of 8,192 and 126 of 1,000 264 / 102 (258)
 inline AttnSplit attn_split(int64_t batch, int64_t heads, int64_t n_pass, int64_t t_end,
