@@ -188,7 +188,8 @@ tvq_status tvq_decode(const tvq_codec* c, const void* cache, const tvq_layout* l
  * The token range of a (sequence, KV head) is split into spans of whole tiles, one per
  * workgroup, so that a launch has about as many workgroups as the codec's device holds at once
  * (its compute units times the resident workgroups of the layer's formats, taken at
- * tvq_create); the workspace holds one partial (max, sum, d accumulators) per query head and
+ * tvq_create), or a few times as many where the (sequence, KV head) rows do not divide those
+ * well; the workspace holds one partial (max, sum, d accumulators) per query head and
  * span.  Its size is that of a split into equal chunks, one per wave slot (whole tile pairs, at
  * least 4 tiles), which is never fewer than the spans; it depends on the device the codec was
  * created on.

@@ -28,7 +28,7 @@
 // it is.
 // m_g is a reference point shared by the wave, not the running maximum: it is raised (and acc,
 // l rescaled) only when a score exceeds it by more than kLazyLog2, so every weight stays below
-// 2^kLazyLog2 and the rescale runs on a few tiles of a chunk.  The merge kernel combines the
+// 2^kLazyLog2 and the rescale runs on a few tiles of a wave.  The merge kernel combines the
 // spans of each output, M = max m_c, L = sum l_c 2^(m_c - M), A = sum acc_c 2^(m_c - M), and
 // stores D W (A / L).  The next tile's codes load while the current one is worked on.  All
 // arithmetic is fp32; scores are in log2 units so each weight is one v_exp_f32.
@@ -126,12 +126,12 @@ struct SeqColumns {
   uint32_t ctx;                  // the sequence's context
 };
 
-// The columns of sequence `want` (BY_SEQ), or of the sequence whose columns (column) `want` lies
-// in or, with no spare columns, behind; count 0 when there is none.  Uniform; every lane of the
-// wave takes part.  With spare columns lane i looks after k consecutive sequences, k = ceil(B / 64):
-// their tiles are added up, then their columns, and where k > 1 the sequences of the lane that
-// holds `want` are looked up one per lane: the lookup adds up over the wave two or three times,
-// whatever the batch.
+// The columns of sequence `want` (BY_SEQ), or of the sequence that holds column `want`: a column that
+// no sequence uses lies outside [first, first + count).  Uniform; every lane of the wave takes
+// part.  With spare columns lane i looks after k = ceil(B / 64) consecutive sequences: their tiles
+// are added up, then their columns, and where k > 1 the sequences of the lane that holds `want`
+// are looked up one per lane, so that the wave scans two or three times, whatever the batch (512
+// sequences, 8 KV heads: 75 us a layer, 80 with a load and two scans per 64 sequences).
 template <int D, bool BY_SEQ>
 __device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t want) {
   constexpr uint32_t VPW = AttnWave<D>::VPW;
@@ -206,7 +206,7 @@ __device__ __forceinline__ u32x2 v_header(const AttnArgs& a, const AttnWave<D>& 
 // the same for the whole wave, and a tile lies inside one pool block of a paged cache (blocks
 // hold a multiple of a tile's tokens; the block's pool index comes from lane i of w.blk), so
 // the record addresses of its first token are scalar and a lane adds its own token's offset.
-// Slots past the chunk read its last token (in bounds) and get weight 0.
+// Slots past the wave's tokens read its last one (in bounds) and get weight 0.
 template <int D, int KW, int KN, int VW, int VN>
 __device__ __forceinline__ TilePair<KW, KN, VW, VN> tile_pair(const AttnArgs& a,
                                                               const AttnWave<D>& w,
@@ -642,7 +642,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
       if constexpr (D == 128) v += row_ror<4>(v);
       sv[q] = v;
     }
-    if (ragged && tile == last) {              // tokens past the chunk weigh 0
+    if (ragged && tile == last) {              // tokens past the wave's weigh 0
 #pragma unroll
       for (int q = 0; q < 4; ++q) sv[q] = tile * VPW + (tok - x) + q < w.ntok ? sv[q] : -INFINITY;
     }
