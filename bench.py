@@ -24,6 +24,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -327,9 +328,12 @@ def _short(name: str) -> str:
 
 def _kernel_label(name: str) -> str:
     """"void tvq::(anonymous namespace)::encode_fast_kernel<128, true>(tvq::EncodeArgs)" ->
-    "encode_fast_kernel<128, true>"."""
-    name = name.split("(tvq::")[0]
-    return name.split("::")[-1]
+    "encode_fast_kernel<128, true>"; a template argument of an enumeration, written with its type
+    in parentheses, keeps its value."""
+    m = re.search(r"::(\w+<.*>)\(tvq::\w+\)$", name)
+    if m is None:
+        return name.split("(tvq::")[0].split("::")[-1]
+    return re.sub(r"\((?:[^()]|\([^()]*\))*\)", "", m.group(1))
 
 
 def _find(dirpath: str, suffix: str) -> str:

@@ -103,3 +103,17 @@ def test_codec_counter_summaries_exist_for_their_workloads():
     d = json.load(open(b.LONGCTX_DECODE_COUNTERS))
     assert d["workload"] == workloads.get("C5").name
     assert 1.0 <= d["hbm_bytes_per_step"] / d["algorithmic_bytes_per_step"] < 1.1
+
+
+@pytest.mark.parametrize("name,label", [
+    ("void tvq::(anonymous namespace)::encode_fast_kernel<128, true, false, "
+     "(tvq::(anonymous namespace)::Tiles)1, false>(tvq::EncodeArgs)",
+     "encode_fast_kernel<128, true, false, 1, false>"),
+    ("void tvq::(anonymous namespace)::decode_fast_kernel<64, false, true, true, false>"
+     "(tvq::DecodeArgs)", "decode_fast_kernel<64, false, true, true, false>"),
+    ("void tvq::(anonymous namespace)::attn_merge_kernel<128>(tvq::AttnArgs)",
+     "attn_merge_kernel<128>"),
+])
+def test_kernel_labels(name, label):
+    """The kernel names of a profile, with enumerations among the template arguments."""
+    assert _bench()._kernel_label(name) == label
