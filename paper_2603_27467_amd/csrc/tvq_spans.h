@@ -47,14 +47,22 @@ TVQ_HOST_DEVICE uint32_t span_count(uint32_t T, uint32_t total, uint32_t spare, 
   return n > c ? n : c;
 }
 
-// Workgroup `unit` (passes aside) takes KV head unit % heads of column unit / heads: the columns of
-// a long sequence then lie side by side over all XCDs and compute units.  Ordered by head first,
-// the heads' columns of a sequence were n_part apart, a multiple of the XCDs and of an XCD's
-// places as a rule, and met on the same compute units.  8 KV heads, d = 128, us a layer, heads
-// first / columns first: 2 sequences of 8,192 tokens among 126 of 1,000, a column each 442 / 264;
-// 4 of 8,192 among 512 506 / 330; 16 of 8,193 to 32,770 222 / 201; 64 of 75 to 300 26 / 19.
-TVQ_HOST_DEVICE uint32_t unit_column(uint32_t unit, uint32_t heads) { return unit / heads; }
-TVQ_HOST_DEVICE uint32_t unit_head(uint32_t unit, uint32_t heads) { return unit % heads; }
+// Column and KV head of workgroup `unit` (passes aside).  Where the contexts differ the columns go
+// first, a column's heads side by side, so that the columns of a long sequence lie together and
+// go round all XCDs and compute units.  Ordered by head first, they were n_part apart for the
+// heads, a multiple of the XCDs and of an XCD's places as a rule, and met on the same compute
+// units.  8 KV heads, d = 128, us a layer, heads first / columns first: 2 sequences of 8,192
+// tokens among 126 of 1,000, a column each 442 / 264; 4 of 8,192 among 512 506 / 330; 16 of 8,193
+// to 32,770 222 / 201; 64 of 75 to 300 26 / 19.  Equal contexts keep the heads first: neighbours
+// then read neighbouring records (8 sequences of 8,195 tokens, d = 64, six layers: 171 / 172.6).
+TVQ_HOST_DEVICE uint32_t unit_column(uint32_t unit, uint32_t heads, uint32_t n_part,
+                                     bool columns_first) {
+  return columns_first ? unit / heads : unit % n_part;
+}
+TVQ_HOST_DEVICE uint32_t unit_head(uint32_t unit, uint32_t heads, uint32_t n_part,
+                                   bool columns_first) {
+  return columns_first ? unit % heads : unit / n_part;
+}
 
 struct AttnSplit {
   int64_t chunk, n_chunks;                       // of the workspace rule

@@ -20,7 +20,8 @@ extern "C" void counts(const uint32_t* tiles, int64_t batch, uint32_t spare, uin
                         : tvq::span_count(tiles[b], total, spare, max_span, min_log2);
 }
 
-extern "C" void unit(uint32_t u, uint32_t heads, uint32_t* column_and_head) {
-  column_and_head[0] = tvq::unit_column(u, heads);
-  column_and_head[1] = tvq::unit_head(u, heads);
+extern "C" void unit(uint32_t u, uint32_t heads, uint32_t n_part, int columns_first,
+                     uint32_t* column_and_head) {
+  column_and_head[0] = tvq::unit_column(u, heads, n_part, columns_first != 0);
+  column_and_head[1] = tvq::unit_head(u, heads, n_part, columns_first != 0);
 }

@@ -23,7 +23,7 @@ class Split:
     def __init__(self, so):
         self.lib = ctypes.CDLL(so)
         self.lib.split.argtypes = [ctypes.c_int64] * 7 + [ctypes.c_void_p]
-        self.lib.unit.argtypes = [ctypes.c_uint32] * 2 + [ctypes.c_void_p]
+        self.lib.unit.argtypes = [ctypes.c_uint32] * 3 + [ctypes.c_int, ctypes.c_void_p]
         self.lib.counts.argtypes = [ctypes.c_void_p, ctypes.c_int64] + [ctypes.c_uint32] * 3 + \
             [ctypes.c_void_p]
 
@@ -32,9 +32,9 @@ class Split:
         self.lib.split(*args, out.ctypes.data)
         return dict(zip(self.FIELDS, (int(x) for x in out)))
 
-    def unit(self, u, heads):
+    def unit(self, u, heads, n_part, columns_first):
         out = np.zeros(2, np.uint32)
-        self.lib.unit(u, heads, out.ctypes.data)
+        self.lib.unit(u, heads, n_part, columns_first, out.ctypes.data)
         return int(out[0]), int(out[1])
 
     def counts(self, tiles, p):
@@ -120,14 +120,13 @@ def test_rows_that_do_not_divide_the_device(spans, B, H, n_pass, block):
 
 @pytest.mark.parametrize("H", [1, 2, 8, 32])
 def test_units_of_a_sequence_are_neighbours(spans, H):
-    """Every (column, head) has one unit, and the units of a column are consecutive, so that one
-    long sequence's workgroups go round the XCDs and their compute units."""
+    """Every (column, head) has one unit in either order, and where the contexts differ the units
+    of a column are consecutive, so that one long sequence's workgroups go round the XCDs and
+    their compute units."""
     n_part = 129
-    units = [spans.unit(u, H) for u in range(n_part * H)]
-    assert sorted(units) == [(c, h) for c in range(n_part) for h in range(H)]
-    for c in range(n_part):
-        at = [u for u, (col, _) in enumerate(units) if col == c]
-        assert at == list(range(at[0], at[0] + H))
+    every = [(c, h) for c in range(n_part) for h in range(H)]
+    assert sorted(spans.unit(u, H, n_part, 0) for u in range(n_part * H)) == every
+    assert [spans.unit(u, H, n_part, 1) for u in range(n_part * H)] == every
 
 
 @pytest.mark.gpu
