@@ -884,7 +884,7 @@ def _attention_check(s, lay, cache, q, layer, t_end, scale, name, q_dtype=None, 
 def test_attention_matches_oracle(gpu, d, G, T, fmt):
     """Attention of one query token over the compressed cache (query heads grouped over the
     KV heads), from the codes, against the oracle's fp64 attention over the decoded cache:
-    several chunks with a ragged last one, one token, and a short range.  The formats cover
+    several spans with a ragged last tile, one token, and a short range.  The formats cover
     every table of the kernel at both d (log-space levels of K and of V, n = 64 and 256) and G
     covers whole, partial (G = 6: two passes of 3 heads) and single-head passes, up to the
     largest group the kernels take (64 query heads per KV head)."""
@@ -1036,7 +1036,7 @@ def test_long_context_attention_full_size_sampled(gpu, wl, need_gb):
     8 sequences x 8192 + 1 tokens, 16 layers x 8 KV heads, d = 64, keys of layers 0-3 at
     n = 256; 32 query heads.  Contiguous cache and paged pool (256-slot blocks, shuffled tables)
     encoded from the same draw; attention of a boosted and a base layer.  The paged outputs
-    equal the contiguous ones bit for bit (same chunk plan, same codes); sampled (sequence, KV
+    equal the contiguous ones bit for bit (same spans, same codes); sampled (sequence, KV
     head) rows are checked against the oracle's fp64 attention over that row's records
     (gathered on the GPU), under parity.attention_error_bar.  C5 needs ~140 GB of device
     memory."""

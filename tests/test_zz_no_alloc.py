@@ -1,6 +1,6 @@
 """tvq_attention_decode_noalloc (attention with the library's static scratch in place of a
 caller's workspace), through the C ABI, against tvq_attention_decode with a workspace: the
-same kernels and chunk plan, so the outputs must be identical bit for bit, on two calls in a
+same kernels and spans, so the outputs must be identical bit for bit, on two calls in a
 row (the second smaller, so it reads partials the first call left behind only if it failed to
 write its own), and within the oracle's attention bar.  A call whose partials exceed the
 scratch is refused before any launch."""
