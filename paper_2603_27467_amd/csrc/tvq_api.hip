@@ -622,7 +622,8 @@ static tvq_status encode_launch(const tvq_codec* c, tvq::EncodeArgs& a, const tv
 }
 
 // Contiguous ranges of at least this many vectors per kind whose token count is not a multiple
-// of the tile's are encoded or decoded in two parts (whole tiles per (batch, head) row, on the
+// of the tile's (of a pool: whose rows are too short for row tiles, decode only) are encoded or
+// decoded in two parts (whole tiles per (batch, head) row, on the
 // kernels that keep a tile's position in scalar registers, then the remaining tokens of every
 // row): below it the extra launch costs more than those kernels save.
 constexpr int64_t kSplitVectors = 1 << 19;
@@ -823,6 +824,27 @@ tvq_status tvq_decode_paged(const tvq_codec* c, const void* pool, const tvq_layo
   a.n_slots = pool_layout->batch * c->H * pool_layout->capacity_tokens;
   a.cap = (uint32_t)pool_layout->capacity_tokens;
   a.t_begin = (uint32_t)t_begin;
+  // As tvq_decode: a large range from a tile boundary of rows too short for row tiles of their own
+  // (row_tiles) is decoded as its whole tiles per row (one block lookup per tile), then the
+  // remaining tokens of every row.  530,000 vectors per kind and layer, two layers, two parts /
+  // one launch of packed tiles, us: d = 128, rows of 33 tokens 176 / 197, 65: 169 / 189, 113:
+  // 165 / 187; d = 64, 33: 99 / 126, 129: 90 / 106.
+  const int64_t vpw = tvq::kWave / (c->d / tvq::kElemsPerLane);
+  const int64_t whole = out->tokens / vpw * vpw;
+  if (t_begin % vpw == 0 && whole > 0 && out->batch * c->H * whole >= kSplitVectors &&
+      !tvq::row_tiles((uint64_t)out->tokens, (uint64_t)((out->tokens + vpw - 1) / vpw),
+                      (uint64_t)vpw, true)) {
+    tvq_tensor_desc head = *out, tail = *out;
+    head.tokens = whole;
+    tail.tokens = out->tokens - whole;
+    tvq::DecodeArgs b = a;
+    const tvq_status st = decode_launch(c, a, &head, out_dtype, k_out, v_out, stream);
+    if (st != TVQ_OK) return st;
+    b.t_begin = (uint32_t)(t_begin + whole);
+    const int64_t skip = whole * out->stride_t * eb;   // bytes of the head's tokens in a row
+    return decode_launch(c, b, &tail, out_dtype, (char*)k_out + skip, (char*)v_out + skip,
+                         stream);
+  }
   return decode_launch(c, a, out, out_dtype, k_out, v_out, stream);
 }
 
