@@ -126,21 +126,30 @@ struct SeqColumns {
   uint32_t ctx;                  // the sequence's context
 };
 
-// The columns of sequence `want` (BY_SEQ), or of the sequence that holds column `want`: a column that
-// no sequence uses lies outside [first, first + count).  Uniform; every lane of the wave takes
-// part.  With spare columns lane i looks after k = ceil(B / 64) consecutive sequences: their tiles
-// are added up, then their columns, and where k > 1 the sequences of the lane that holds `want`
-// are looked up one per lane, so that the wave scans two or three times, whatever the batch (512
-// sequences, 8 KV heads: 75 us a layer, 80 with a load and two scans per 64 sequences).
-template <int D, bool BY_SEQ>
-__device__ __forceinline__ SeqColumns seq_columns(const AttnArgs& a, uint32_t want) {
+// How a call's columns are found (tvq_spans.h).  Kernels of their own: the start of a launch is a
+// chain of cold fetches, of code too, and the lookup of shared columns in the way of the others
+// cost them 0.3 to 0.5 us a layer (32 sequences of 100 tokens 9.9 -> 10.4 us).
+enum Columns { kOwnColumns, kSharedColumns };
+
+// The columns of sequence b with nothing to share: per_seq of them, of which it uses all (equal
+// contexts) or as many as its own context takes.
+template <int D>
+__device__ __forceinline__ SeqColumns own_columns(const AttnArgs& a, uint32_t b) {
   constexpr uint32_t VPW = AttnWave<D>::VPW;
-  if (__builtin_expect(a.spare == 0, 1)) {       // the short way lies next in the code
-    const uint32_t b = BY_SEQ ? want : want / a.per_seq;
-    if (!a.pg.seq) return SeqColumns{b, b * a.per_seq, a.per_seq, a.t_end};
-    const uint32_t ctx = seq_context(a, b);
-    return SeqColumns{b, b * a.per_seq, span_floor((ctx + VPW - 1) / VPW, a.max_span), ctx};
-  }
+  if (!a.pg.seq) return SeqColumns{b, b * a.per_seq, a.per_seq, a.t_end};
+  const uint32_t ctx = seq_context(a, b);
+  return SeqColumns{b, b * a.per_seq, span_floor((ctx + VPW - 1) / VPW, a.max_span), ctx};
+}
+
+// Shared columns: those of sequence `want` (BY_SEQ), or of the sequence that holds column `want`
+// (count 0 when none does).  Uniform; every lane of the wave takes part.  Lane i looks after
+// k = ceil(B / 64) consecutive sequences: their tiles are added up, then their columns, and where
+// k > 1 the sequences of the lane that holds `want` are looked up one per lane, so that the wave
+// scans two or three times, whatever the batch (512 sequences, 8 KV heads: 75 us a layer, 80 with
+// a load and two scans per 64 sequences).
+template <int D, bool BY_SEQ>
+__device__ __forceinline__ SeqColumns shared_columns(const AttnArgs& a, uint32_t want) {
+  constexpr uint32_t VPW = AttnWave<D>::VPW;
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t k = (a.B + kWave - 1) / kWave;
   auto context = [&](uint32_t b) { return b < a.B ? seq_context(a, b) : 0u; };
@@ -422,7 +431,7 @@ __device__ __forceinline__ v4f value_quad(const float* lo, const float* hi, cons
   return acc;
 }
 
-template <int D, int KW, int KN, int VW, int VN>
+template <int D, int KW, int KN, int VW, int VN, int COLUMNS>
 __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnArgs a) {
   static_assert(D == 64 || D == 128, "d = 64 or 128");
   constexpr int LPV = AttnWave<D>::LPV;
@@ -446,10 +455,13 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   if (unit >= a.n_part * a.H) return;
   AttnWave<D> w;
   w.lane = lane;
-  w.h = unit_head(unit, a.H, a.n_part, a.pg.seq != nullptr);
-  const uint32_t col = unit_column(unit, a.H, a.n_part, a.pg.seq != nullptr);
-  const SeqColumns sc = seq_columns<D, false>(a, col);
-  if (col - sc.first >= sc.count) return;
+  const bool columns_first = COLUMNS == kSharedColumns || a.pg.seq != nullptr;
+  const UnitOf uh = unit_of(unit, a.H, a.n_part, columns_first);
+  w.h = uh.head;
+  const uint32_t col = uh.column;
+  const SeqColumns sc = COLUMNS == kSharedColumns ? shared_columns<D, false>(a, col)
+                                                  : own_columns<D>(a, col / a.per_seq);
+  if (col - sc.first >= sc.count) return;        // a column that no sequence uses
   w.b = sc.b;
   // the span's tiles, then the wave's: as even as whole tiles allow
   const uint32_t ctx = sc.ctx;
@@ -779,7 +791,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
 // contiguous rows and summed without any exchange between lanes.  The spans' (m_c, l_c) are
 // read 64 at a time, one per lane: M = max m_c, then the weights 2^(m_c - M), L, and each
 // span's weight taken from its lane by a scalar read.  o = D W (A / L).
-template <int D>
+template <int D, int COLUMNS>
 __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
   constexpr int EPL = D / kWave;                      // elements per lane: 1 or 2
   const int lane = threadIdx.x & (kWave - 1);
@@ -787,7 +799,8 @@ __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
                                                      threadIdx.x / kWave);
   if (j >= a.B * a.Hq) return;
   const uint32_t b = j / a.Hq;
-  const SeqColumns sc = seq_columns<D, true>(a, b);
+  const SeqColumns sc = COLUMNS == kSharedColumns ? shared_columns<D, true>(a, b)
+                                                  : own_columns<D>(a, b);
   const uint32_t nc = sc.count;
   const uint64_t col0 = (uint64_t)(j - b * a.Hq) * a.n_part + sc.first;
   const float2* const ml = (const float2*)(a.ws_ml + col0 * 2);
@@ -839,8 +852,21 @@ __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
 
 template <int D, int KW, int KN, int VW, int VN>
 void launch_chunk(const AttnArgs& a, dim3 grid, hipStream_t s) {
-  hipLaunchKernelGGL((attn_mfma_chunk_kernel<D, KW, KN, VW, VN>), grid, dim3(kBlockThreads), 0, s,
-                     a);
+  const dim3 block(kBlockThreads);
+  if (a.spare != 0)
+    hipLaunchKernelGGL((attn_mfma_chunk_kernel<D, KW, KN, VW, VN, kSharedColumns>), grid, block, 0,
+                       s, a);
+  else
+    hipLaunchKernelGGL((attn_mfma_chunk_kernel<D, KW, KN, VW, VN, kOwnColumns>), grid, block, 0, s,
+                       a);
+}
+
+template <int D>
+void launch_merge(const AttnArgs& a, hipStream_t s) {
+  const uint64_t waves = (uint64_t)a.B * a.Hq;
+  const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock)), block(kBlockThreads);
+  if (a.spare != 0) hipLaunchKernelGGL((attn_merge_kernel<D, kSharedColumns>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((attn_merge_kernel<D, kOwnColumns>), grid, block, 0, s, a);
 }
 
 // format index: bit 0 = 8-bit angle codes (n = 256), bit 1 = 4-bit log norms
@@ -856,15 +882,16 @@ void launch_chunk_v(const AttnArgs& a, int vf, dim3 grid, hipStream_t s) {
 }
 
 // Workgroups of the chunk kernel for key format KF and value format vf that one compute unit
-// holds at once; 0 on a HIP error.
+// holds at once (its launch bounds and LDS are the same for both kinds of columns); 0 on a HIP
+// error.
 template <int D, int KF>
 int chunk_blocks_v(int vf) {
   constexpr int KW = (KF & 1) ? 8 : 6, KN = (KF & 2) ? 4 : 8;
   const void* f[4];
-  f[0] = (const void*)attn_mfma_chunk_kernel<D, KW, KN, 6, 8>;
-  f[1] = (const void*)attn_mfma_chunk_kernel<D, KW, KN, 8, 8>;
-  f[2] = (const void*)attn_mfma_chunk_kernel<D, KW, KN, 6, 4>;
-  f[3] = (const void*)attn_mfma_chunk_kernel<D, KW, KN, 8, 4>;
+  f[0] = (const void*)attn_mfma_chunk_kernel<D, KW, KN, 6, 8, kOwnColumns>;
+  f[1] = (const void*)attn_mfma_chunk_kernel<D, KW, KN, 8, 8, kOwnColumns>;
+  f[2] = (const void*)attn_mfma_chunk_kernel<D, KW, KN, 6, 4, kOwnColumns>;
+  f[3] = (const void*)attn_mfma_chunk_kernel<D, KW, KN, 8, 4, kOwnColumns>;
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f[vf & 3], kBlockThreads, 0) != hipSuccess)
     return 0;
@@ -906,15 +933,12 @@ int tvq_launch_attention(const tvq::AttnArgs& a, int d, int k_format, int v_form
   // units (column and KV head) go round the XCDs in eights, the passes of one eight in turn
   const uint64_t units = (uint64_t)a.H * a.n_part;
   const dim3 grid1((unsigned)((units + 7) / 8 * 8 * a.n_pass));
-  const uint64_t merge_waves = (uint64_t)a.B * a.Hq;
-  const dim3 grid2((unsigned)((merge_waves + tvq::kWavesPerBlock - 1) / tvq::kWavesPerBlock));
-  const dim3 block(tvq::kBlockThreads);
   if (d == 128) tvq::launch_chunk_kv<128>(a, k_format, v_format, grid1, s);
   else if (d == 64) tvq::launch_chunk_kv<64>(a, k_format, v_format, grid1, s);
   else return -1;
   if (hipGetLastError() != hipSuccess) return -2;
   if (a.direct) return 0;
-  if (d == 128) hipLaunchKernelGGL(tvq::attn_merge_kernel<128>, grid2, block, 0, s, a);
-  else hipLaunchKernelGGL(tvq::attn_merge_kernel<64>, grid2, block, 0, s, a);
+  if (d == 128) tvq::launch_merge<128>(a, s);
+  else tvq::launch_merge<64>(a, s);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }

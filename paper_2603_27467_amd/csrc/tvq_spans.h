@@ -55,13 +55,14 @@ TVQ_HOST_DEVICE uint32_t span_count(uint32_t T, uint32_t total, uint32_t spare, 
 // tokens among 126 of 1,000, a column each 442 / 264; 4 of 8,192 among 512 506 / 330; 16 of 8,193
 // to 32,770 222 / 201; 64 of 75 to 300 26 / 19.  Equal contexts keep the heads first: neighbours
 // then read neighbouring records (8 sequences of 8,195 tokens, d = 64, six layers: 171 / 172.6).
-TVQ_HOST_DEVICE uint32_t unit_column(uint32_t unit, uint32_t heads, uint32_t n_part,
-                                     bool columns_first) {
-  return columns_first ? unit / heads : unit % n_part;
-}
-TVQ_HOST_DEVICE uint32_t unit_head(uint32_t unit, uint32_t heads, uint32_t n_part,
-                                   bool columns_first) {
-  return columns_first ? unit % heads : unit / n_part;
+struct UnitOf {
+  uint32_t column, head;
+};
+TVQ_HOST_DEVICE UnitOf unit_of(uint32_t unit, uint32_t heads, uint32_t n_part,
+                               bool columns_first) {
+  const uint32_t div = columns_first ? heads : n_part;
+  const uint32_t q = unit / div, r = unit - q * div;
+  return columns_first ? UnitOf{q, r} : UnitOf{r, q};
 }
 
 struct AttnSplit {

@@ -22,6 +22,7 @@ extern "C" void counts(const uint32_t* tiles, int64_t batch, uint32_t spare, uin
 
 extern "C" void unit(uint32_t u, uint32_t heads, uint32_t n_part, int columns_first,
                      uint32_t* column_and_head) {
-  column_and_head[0] = tvq::unit_column(u, heads, n_part, columns_first != 0);
-  column_and_head[1] = tvq::unit_head(u, heads, n_part, columns_first != 0);
+  const tvq::UnitOf of = tvq::unit_of(u, heads, n_part, columns_first != 0);
+  column_and_head[0] = of.column;
+  column_and_head[1] = of.head;
 }
