@@ -199,7 +199,7 @@ tvq_status tvq_decode(const tvq_codec* c, const void* cache, const tvq_layout* l
  * fp64 evaluation).
  * Supported: d = 64 or 128, G <= 64, and for both K and V of the layer n = 64 or 256 with
  * 8-bit linear or 4-bit log-space norms (TVQ_ERR_UNSUPPORTED otherwise).  Launches two
- * kernels on `stream`, one where every sequence is a single span. */
+ * kernels on `stream`, one where every (sequence, KV head) is a single span or wave. */
 tvq_status tvq_attention_workspace(const tvq_codec* c, int64_t batch, int32_t num_q_heads,
                                    int64_t t_end, int64_t* bytes);
 tvq_status tvq_attention_decode(const tvq_codec* c, const void* cache, const tvq_layout* lay,

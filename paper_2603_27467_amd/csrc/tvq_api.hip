@@ -955,7 +955,7 @@ static tvq_status attention_launch(const tvq_codec* c, tvq::AttnArgs& a, const v
   a.min_log2 = (uint32_t)p.split.min_log2;
   a.pass_heads = p.pass_heads;
   a.n_pass = p.n_pass;
-  a.direct = p.split.n_part == batch ? 1u : 0u;
+  a.direct = p.split.n_part <= batch ? 1u : 0u;
   a.q_f32 = q_dtype == TVQ_F32 ? 1u : 0u;
   a.o_f32 = o_dtype == TVQ_F32 ? 1u : 0u;
   a.qscale = scale * 1.4426950408889634f;          // scores in log2 units

@@ -16,13 +16,15 @@
 // head) for up to four of the G query heads (G > 4 runs in passes of balanced size), its four
 // waves as even a share each as whole tiles allow.  The spans of a sequence hold the same number
 // of tiles to within one, those of different sequences up to the share that tvq_spans.h states,
-// also where the contexts differ and are known to the device only.
+// also where the contexts differ and are known to the device only.  Many rows of short contexts
+// take a wave each instead (kRowWaves).
 //   prologue  q^_g = scale * log2(e) * W D q_g into LDS, one head per wave; the loads that the
 //             first tile needs are issued before any of them is waited for
 //   per tile  y'_K from the K codes, the scores s_g = q^_g . y'_K, then y'_V from the V codes
 //             and, per head, acc_g += 2^(s_g - m_g) y'_V and l_g += 2^(s_g - m_g)
 //   out       the waves' (m, l, acc[d]) summed in LDS, one partial per query head and span into
-//             the workspace; a launch whose sequences are one span each stores its outputs
+//             the workspace; a launch whose sequences are one span (or wave) each stores its
+//             outputs
 // The chunk kernel (attn_mfma_chunk_kernel) does both contractions on the matrix cores, 16
 // tokens (d = 128) or 32 tokens (d = 64) x 4 heads per tile; its layouts are described where
 // it is.
@@ -126,10 +128,11 @@ struct SeqColumns {
   uint32_t ctx;                  // the sequence's context
 };
 
-// How a call's columns are found (tvq_spans.h).  Kernels of their own: the start of a launch is a
-// chain of cold fetches, of code too, and the lookup of shared columns in the way of the others
-// cost them 0.3 to 0.5 us a layer (32 sequences of 100 tokens 9.9 -> 10.4 us).
-enum Columns { kOwnColumns, kSharedColumns };
+// How a call's columns are found (tvq_spans.h); kRowWaves: a wave takes a whole row (sequence, KV
+// head, pass) instead.  Kernels of their own: the start of a launch is a chain of cold fetches, of
+// code too, and the lookup of shared columns in the way of the others cost them 0.3 to 0.5 us a
+// layer (32 sequences of 100 tokens 9.9 -> 10.4 us).
+enum Columns { kOwnColumns, kSharedColumns, kRowWaves };
 
 // The columns of sequence b with nothing to share: per_seq of them, of which it uses all (equal
 // contexts) or as many as its own context takes.
@@ -446,32 +449,49 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   __builtin_amdgcn_s_setprio(3);
   const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x & (kWave - 1);
-  // the workgroup's column, KV head and pass.  The passes of one span read the same codes: they
-  // are 8 workgroups apart, on the same XCD (workgroups go round the 8 XCDs), so the later ones
-  // find them in its L2.
-  const uint32_t q8 = blockIdx.x >> 3;
-  const uint32_t pass = q8 % a.n_pass;
-  const uint32_t unit = (q8 / a.n_pass) * 8 + (blockIdx.x & 7u);
-  if (unit >= a.n_part * a.H) return;
   AttnWave<D> w;
   w.lane = lane;
-  const bool columns_first = COLUMNS == kSharedColumns || a.pg.seq != nullptr;
-  const UnitOf uh = unit_of(unit, a.H, a.n_part, columns_first);
-  w.h = uh.head;
-  const uint32_t col = uh.column;
-  const SeqColumns sc = COLUMNS == kSharedColumns ? shared_columns<D, false>(a, col)
-                                                  : own_columns<D>(a, col / a.per_seq);
-  if (col - sc.first >= sc.count) return;        // a column that no sequence uses
-  w.b = sc.b;
-  // the span's tiles, then the wave's: as even as whole tiles allow
-  const uint32_t ctx = sc.ctx;
-  const uint32_t tiles = (ctx + VPW - 1) / VPW;
-  const uint32_t k = col - sc.first;
-  const uint32_t per = tiles / sc.count, extra = tiles - per * sc.count;
-  const uint32_t span0 = k * per + min(k, extra), span = per + (k < extra ? 1u : 0u);
-  const uint32_t wper = span / kWavesPerBlock, wextra = span % kWavesPerBlock;
-  const uint32_t nt = wper + (wib < wextra ? 1u : 0u);
-  w.t0 = nt != 0 ? (span0 + wib * wper + min(wib, wextra)) * VPW : 0u;
+  uint32_t pass, col = 0, ctx, tile0, nt;            // the wave's tiles [tile0, tile0 + nt)
+  bool active = true;
+  if constexpr (COLUMNS == kRowWaves) {
+    // the passes of one row are neighbours; a wave past the last row works on that one's token 0
+    // and stores nothing
+    const uint32_t i = blockIdx.x * kWavesPerBlock + wib, n = a.B * a.H * a.n_pass;
+    active = i < n;
+    const uint32_t row = min(i, n - 1) / a.n_pass;
+    pass = min(i, n - 1) - row * a.n_pass;
+    w.b = row / a.H;
+    w.h = row - w.b * a.H;
+    ctx = seq_context(a, w.b);
+    tile0 = 0;
+    nt = active ? (ctx + VPW - 1) / VPW : 0u;
+  } else {
+    // the workgroup's column, KV head and pass.  The passes of one span read the same codes: they
+    // are 8 workgroups apart, on the same XCD (workgroups go round the 8 XCDs), so the later ones
+    // find them in its L2.
+    const uint32_t q8 = blockIdx.x >> 3;
+    pass = q8 % a.n_pass;
+    const uint32_t unit = (q8 / a.n_pass) * 8 + (blockIdx.x & 7u);
+    if (unit >= a.n_part * a.H) return;
+    const bool columns_first = COLUMNS == kSharedColumns || a.pg.seq != nullptr;
+    const UnitOf uh = unit_of(unit, a.H, a.n_part, columns_first);
+    w.h = uh.head;
+    col = uh.column;
+    const SeqColumns sc = COLUMNS == kSharedColumns ? shared_columns<D, false>(a, col)
+                                                    : own_columns<D>(a, col / a.per_seq);
+    if (col - sc.first >= sc.count) return;        // a column that no sequence uses
+    w.b = sc.b;
+    // the span's tiles, then the wave's: as even as whole tiles allow
+    ctx = sc.ctx;
+    const uint32_t tiles = (ctx + VPW - 1) / VPW;
+    const uint32_t k = col - sc.first;
+    const uint32_t per = tiles / sc.count, extra = tiles - per * sc.count;
+    const uint32_t span0 = k * per + min(k, extra), span = per + (k < extra ? 1u : 0u);
+    const uint32_t wper = span / kWavesPerBlock, wextra = span % kWavesPerBlock;
+    nt = wper + (wib < wextra ? 1u : 0u);
+    tile0 = span0 + wib * wper + min(wib, wextra);
+  }
+  w.t0 = nt != 0 ? tile0 * VPW : 0u;
   w.ntok = nt != 0 ? min(nt * VPW, ctx - w.t0) : 1u;   // no tile: token 0 is loaded, not used
   w.row = (w.b * a.H + w.h) * a.cap;
   const uint32_t g0 = pass * a.pass_heads;
@@ -489,10 +509,14 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   // everything the first tile needs is requested before any of it is used: the query head of
   // this wave, the tables, the first tile's codes and the first V headers
   constexpr int EPL = D / kWave;
-  const uint64_t head = (uint64_t)w.b * a.Hq + w.h * a.G + g0 + (wib < gc ? wib : 0u);
+  constexpr int NQ = COLUMNS == kRowWaves ? kAttnPassHeads : 1;   // query heads of a wave
+  const uint32_t i0 = COLUMNS == kRowWaves ? 0u : wib;            // the first, in the pass
+  const uint64_t head0 = (uint64_t)w.b * a.Hq + w.h * a.G + g0;
   const uint32_t smw = a.signs[(EPL * lane) / 2];
-  float qx[EPL];
-  load_query<D>(a, head * D, lane, qx);
+  float qx[NQ][EPL];
+#pragma unroll
+  for (uint32_t i = 0; i < NQ; ++i)
+    load_query<D>(a, (head0 + (i0 + i < gc ? i0 + i : 0u)) * D, lane, qx[i]);
   const uint32_t ek = threadIdx.x & ((1u << KW) - 1u), ev = threadIdx.x & ((1u << VW) - 1u);
   const float2 tk = ((const float2*)a.lut[0])[ek];
   float2 tv;
@@ -515,18 +539,28 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   TilePair<KW, KN, VW, VN> ca = tile_pair<D, KW, KN, VW, VN>(a, w, 0);
 
   // q^_g = scale * log2(e) * W D q_g of the pass's heads, head g0 + i by wave i, into every
-  // wave's LDS; the tables, the same for the workgroup
-  apply_signs<EPL>(qx, smw, lane);
-  fwht_across_lanes<EPL>(qx, lane);
+  // wave's LDS (kRowWaves: all of them by the wave, into its own); the tables, the same for the
+  // workgroup
+#pragma unroll
+  for (uint32_t i = 0; i < NQ; ++i) {
+    apply_signs<EPL>(qx[i], smw, lane);
+    fwht_across_lanes<EPL>(qx[i], lane);
+  }
   s_lut_k[ek] = tk;                              // lanes past the table store its values again
   if constexpr (!kShared) s_lut_v[ev] = tv;
-  if (wib < gc) {
-    const int e0 = EPL * lane;                   // slice e0 / 32, element e0 % 32 of it
-    const int at = (wib * LPV + e0 / kElemsPerLane) * kQPitch + e0 % kElemsPerLane;
 #pragma unroll
-    for (int v = 0; v < kWavesPerBlock; ++v)
+  for (uint32_t i = 0; i < NQ; ++i) {
+    if (i0 + i < gc) {
+      const int e0 = EPL * lane;                 // slice e0 / 32, element e0 % 32 of it
+      const int at = ((i0 + i) * LPV + e0 / kElemsPerLane) * kQPitch + e0 % kElemsPerLane;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) s_wave[v][at + e] = qx[e] * a.qscale;
+      for (int v = 0; v < kWavesPerBlock; ++v) {
+        if (COLUMNS == kRowWaves && v != 0) break;
+        float* const dst = COLUMNS == kRowWaves ? lds : s_wave[v];
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) dst[at + e] = qx[i][e] * a.qscale;
+      }
+    }
   }
   const float2* const lut_v = kShared ? s_lut_k : s_lut_v;
   __syncthreads();
@@ -745,6 +779,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   lsum += __shfl_xor(lsum, 32);
   // the four waves' partials through LDS: lane 4b + j writes elements 8b .. 8b + 7 (d = 128) or
   // 4b .. 4b + 3 (d = 64) of head j, then wave i sums head i over the waves in wave order
+  // (kRowWaves: a wave stores the outputs of its own)
   constexpr int kAccPitch = D + 4;
   constexpr int kMl = kAttnPassHeads * kAccPitch;
   static_assert(kMl + 2 * kAttnPassHeads <= kStageWordsOf<D>, "the partials fit the staging");
@@ -758,6 +793,18 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
         make_float4(acc0[0], acc0[1], acc0[2], acc0[3]);
   }
   if (lane < 4) *(float2*)(lds + kMl + 2 * x) = make_float2(m, lsum);
+  if constexpr (COLUMNS == kRowWaves) {
+    wave_lds_sync();
+    if (!active) return;
+    const uint32_t smo = a.signs[(EPL * lane) / 2];
+    for (uint32_t i = 0; i < gc; ++i) {
+      float ox[EPL];
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) ox[e] = lds[i * kAccPitch + EPL * lane + e];
+      store_output<D>(a, head0 + i, ox, lds[kMl + 2 * i], lds[kMl + 2 * i + 1], smo, lane);
+    }
+    return;
+  }
   __syncthreads();
   if (wib >= gc) return;
   float M = -INFINITY;
@@ -777,7 +824,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void attn_mfma_chunk_kernel(AttnA
   }
   if (a.direct) {
     const uint32_t smo = a.signs[(EPL * lane) / 2];
-    store_output<D>(a, head, ax, M, L, smo, lane);
+    store_output<D>(a, head0 + wib, ax, M, L, smo, lane);
     return;
   }
   const uint64_t idx = (uint64_t)(w.h * a.G + g0 + wib) * a.n_part + col;
@@ -851,9 +898,15 @@ __global__ __launch_bounds__(kBlockThreads) void attn_merge_kernel(AttnArgs a) {
 }
 
 template <int D, int KW, int KN, int VW, int VN>
-void launch_chunk(const AttnArgs& a, dim3 grid, hipStream_t s) {
-  const dim3 block(kBlockThreads);
-  if (a.spare != 0)
+void launch_chunk(const AttnArgs& a, hipStream_t s) {
+  // units (column and KV head) go round the XCDs in eights, the passes of one eight in turn
+  const uint64_t units = (uint64_t)a.H * a.n_part, rows = (uint64_t)a.B * a.H * a.n_pass;
+  const dim3 block(kBlockThreads), grid((unsigned)((units + 7) / 8 * 8 * a.n_pass));
+  const dim3 row_grid((unsigned)((rows + kWavesPerBlock - 1) / kWavesPerBlock));
+  if (a.n_part == 0)
+    hipLaunchKernelGGL((attn_mfma_chunk_kernel<D, KW, KN, VW, VN, kRowWaves>), row_grid, block, 0,
+                       s, a);
+  else if (a.spare != 0)
     hipLaunchKernelGGL((attn_mfma_chunk_kernel<D, KW, KN, VW, VN, kSharedColumns>), grid, block, 0,
                        s, a);
   else
@@ -871,18 +924,18 @@ void launch_merge(const AttnArgs& a, hipStream_t s) {
 
 // format index: bit 0 = 8-bit angle codes (n = 256), bit 1 = 4-bit log norms
 template <int D, int KF>
-void launch_chunk_v(const AttnArgs& a, int vf, dim3 grid, hipStream_t s) {
+void launch_chunk_v(const AttnArgs& a, int vf, hipStream_t s) {
   constexpr int KW = (KF & 1) ? 8 : 6, KN = (KF & 2) ? 4 : 8;
   switch (vf) {
-    case 0: launch_chunk<D, KW, KN, 6, 8>(a, grid, s); break;
-    case 1: launch_chunk<D, KW, KN, 8, 8>(a, grid, s); break;
-    case 2: launch_chunk<D, KW, KN, 6, 4>(a, grid, s); break;
-    default: launch_chunk<D, KW, KN, 8, 4>(a, grid, s); break;
+    case 0: launch_chunk<D, KW, KN, 6, 8>(a, s); break;
+    case 1: launch_chunk<D, KW, KN, 8, 8>(a, s); break;
+    case 2: launch_chunk<D, KW, KN, 6, 4>(a, s); break;
+    default: launch_chunk<D, KW, KN, 8, 4>(a, s); break;
   }
 }
 
 // Workgroups of the chunk kernel for key format KF and value format vf that one compute unit
-// holds at once (its launch bounds and LDS are the same for both kinds of columns); 0 on a HIP
+// holds at once (its launch bounds and LDS are the same for every kind of columns); 0 on a HIP
 // error.
 template <int D, int KF>
 int chunk_blocks_v(int vf) {
@@ -909,12 +962,12 @@ int chunk_blocks(int kf, int vf) {
 }
 
 template <int D>
-void launch_chunk_kv(const AttnArgs& a, int kf, int vf, dim3 grid, hipStream_t s) {
+void launch_chunk_kv(const AttnArgs& a, int kf, int vf, hipStream_t s) {
   switch (kf) {
-    case 0: launch_chunk_v<D, 0>(a, vf, grid, s); break;
-    case 1: launch_chunk_v<D, 1>(a, vf, grid, s); break;
-    case 2: launch_chunk_v<D, 2>(a, vf, grid, s); break;
-    default: launch_chunk_v<D, 3>(a, vf, grid, s); break;
+    case 0: launch_chunk_v<D, 0>(a, vf, s); break;
+    case 1: launch_chunk_v<D, 1>(a, vf, s); break;
+    case 2: launch_chunk_v<D, 2>(a, vf, s); break;
+    default: launch_chunk_v<D, 3>(a, vf, s); break;
   }
 }
 
@@ -930,11 +983,8 @@ int tvq_attention_blocks_per_cu(int d, int k_format, int v_format) {
 int tvq_launch_attention(const tvq::AttnArgs& a, int d, int k_format, int v_format,
                          void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  // units (column and KV head) go round the XCDs in eights, the passes of one eight in turn
-  const uint64_t units = (uint64_t)a.H * a.n_part;
-  const dim3 grid1((unsigned)((units + 7) / 8 * 8 * a.n_pass));
-  if (d == 128) tvq::launch_chunk_kv<128>(a, k_format, v_format, grid1, s);
-  else if (d == 64) tvq::launch_chunk_kv<64>(a, k_format, v_format, grid1, s);
+  if (d == 128) tvq::launch_chunk_kv<128>(a, k_format, v_format, s);
+  else if (d == 64) tvq::launch_chunk_kv<64>(a, k_format, v_format, s);
   else return -1;
   if (hipGetLastError() != hipSuccess) return -2;
   if (a.direct) return 0;

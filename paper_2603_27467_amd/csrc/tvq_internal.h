@@ -129,7 +129,7 @@ struct AttnArgs {
   Paging pg;             // pg.seq: context length per sequence (nullptr: t_end for all)
   uint32_t B, H, G, Hq;
   uint32_t t_end;
-  uint32_t n_part;       // columns of partials per query head
+  uint32_t n_part;       // columns of partials per query head; 0: a wave per row, no partials
   uint32_t per_seq;      // columns of each sequence (spare 0)
   uint32_t spare;        // columns shared by context length (pg.seq not null)
   uint32_t max_span;     // most tiles of a workgroup's span

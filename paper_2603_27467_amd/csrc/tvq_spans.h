@@ -70,7 +70,7 @@ struct AttnSplit {
   int64_t n_part, per_seq, spare, max_span, min_log2;
 };
 
-// The split of a call.  rows: (sequence, KV head, pass over the query heads); vpw: tokens of a
+// The split of a call; n_part = 0: no columns, a wave takes a whole row.  rows: (sequence, KV head, pass over the query heads); vpw: tokens of a
 // tile; block_tokens: of a paged pool (the contexts are then device data and t_end bounds them),
 // 0 for a contiguous cache (every context is t_end); slots: waves that the device holds at once.
 //
@@ -91,6 +91,15 @@ struct AttnSplit {
 //   64: 117 / 103 (142), 100: 164 / 160 (202)
 //   paged, a column a sequence / and a half: 128 of 1,025 to 4,100 186 / 190 (244), 128 of 4,096
 //   275 / 279 (290), 2 of 8,192 and 126 of 1,000 264 / 102 (258)
+// A wave per row, where there are rows for the wave slots and the contexts are short: a row then
+// costs one wave's start instead of four, and nothing is summed over waves; but the longest row
+// is one wave's.  us a layer, a workgroup / a wave per row (chunks), 8 KV heads:
+//   twice as many rows as slots, d = 64, 64 query heads, 512 paged sequences: 2 to 8 tokens 44 / 19
+//   (34), 25 to 100 51 / 32 (44), 250 to 1,000 182 / 174 (178)
+//   as many, d = 128, 32 query heads, 512 sequences: 8 tokens 23 / 12 (23), 100: 43 / 38 (46);
+//   paged, 16 of 500 among 512 of 40: 33 / 71 (78); 600 of 500: 168 / 181 (184)
+//   half as many: 30 tokens 14 / 11 (17), 60: 16 / 16 (22), paged, 100 to 400: 44 / 59 (54); a
+//   quarter: 30 tokens 7.5 / 9.4 (13.5)
 inline AttnSplit attn_split(int64_t batch, int64_t heads, int64_t n_pass, int64_t t_end,
                             int64_t block_tokens, int64_t vpw, int64_t slots) {
   AttnSplit s;
@@ -107,6 +116,11 @@ inline AttnSplit attn_split(int64_t batch, int64_t heads, int64_t n_pass, int64_
   s.n_chunks = ceil_div(t_end, s.chunk);
 
   const int64_t tiles = ceil_div(t_end, vpw);
+  if (2 * rows >= slots && tiles <= (rows >= 2 * slots ? 32 : rows >= slots ? 8 : 4)) {
+    s.n_part = s.spare = s.max_span = s.min_log2 = 0;
+    s.per_seq = 1;
+    return s;
+  }
   s.max_span = kSpanWaves * (max_chunk / vpw);
   s.min_log2 = 2;                                                  // a tile per wave
   const int64_t need = ceil_div(tiles, s.max_span);                // columns of a full context
